@@ -269,6 +269,33 @@ constexpr int cfg_ldspf(int fp64, int M, int kind) {
                : 0;
 }
 
+// Tile kernel: signals (rows) or sub-signals (strided and last passes) of the
+// one tile of a workgroup.  Narrow, so that a small batch spreads over the
+// chip: one wavefront where a signal has at most 64 threads, and 64-byte rows
+// in the multi-pass kinds (at most the tile width of the group layout).
+constexpr int cfg_tile_C(int fp64, int M, int kind) {
+    const int T = M / cfg_E(fp64, M, kind);
+    int c = T >= 64 ? 1 : 64 / T;
+    if (kind == KIND_ROWS) return c;
+    if (c < (fp64 ? 4 : 8)) c = fp64 ? 4 : 8;
+    const int cp = cfg_C(fp64, M, kind);
+    return c < cp ? c : cp;
+}
+// Wavefronts of a tile launch up to which every tile has a workgroup of its
+// own (beyond, a workgroup takes several tiles of its group in turn; measured
+// with 4096 and 16384: 5-15% either way, complex64 N = 4096 gains with the
+// former, N = 1024 with the latter), and wavefronts of a pass kernel's launch
+// up to which tiles replace it (the reasons are at use_tiles).
+#ifndef TFFT_TILE_WAVES
+#define TFFT_TILE_WAVES 8192
+#endif
+#ifndef TFFT_TILE_MAX_WAVES
+#define TFFT_TILE_MAX_WAVES 1024
+#endif
+constexpr int cfg_tile_threads(int fp64, int M, int kind) {
+    return cfg_tile_C(fp64, M, kind) * (M / cfg_E(fp64, M, kind));
+}
+
 // Radix sequence: as many stages of radix E as fit, then one stage of the
 // remaining factor (which divides E).
 constexpr int n_full(int M, int E) { return E <= 1 ? 0 : ilog2c(M) / ilog2c(E); }
@@ -347,6 +374,20 @@ struct PassArgs {
     int32_t pad_;
 };
 
+// What a tile launch needs besides PassArgs: a group's tiles are split over
+// 2^split_log2 workgroups of `rounds` tiles each.
+constexpr int kTickStride = 32;  // tickets a 128-byte line apart: atomics on one line are served one by one
+struct TileArgs {
+    double *part;        // [n_groups << split_log2][5] partial group sums
+    uint32_t *tick;      // [n_groups * kTickStride] parts of the group done, 0 between launches
+    int32_t *state;      // [n_groups] 1 for a group flagged in this execution, else 0
+    int64_t rec0;        // index of the pass's first group among the records
+    int32_t split_log2;
+    int32_t rounds;
+    int32_t fix;         // CORRECT mode
+    int32_t pad_;
+};
+
 // Checksum schemes of a pass kernel (template argument FT).
 enum { FT_NONE = 0, FT_BLOCK = 1, FT_SIGNAL = 2, FT_THREAD = 3 };
 
@@ -399,6 +440,7 @@ void *scratch_address(int device);
 // Host-side launchers (defined in the kernel translation unit).
 hipError_t launch_pass(int fp64, int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st);
 hipError_t launch_correct(int fp64, int M, int kind, const PassArgs &a, int grid, hipStream_t st);
+hipError_t launch_tile(int fp64, int M, int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st);
 hipError_t launch_reset(DevReport *rep, hipStream_t st);
 // Persistent ragged kernel: launch over `grid` workgroups, its resident
 // workgroups per compute unit, and the reset of its queue state and report.

@@ -76,9 +76,9 @@ __device__ __forceinline__ void stg(cx<R> *p, cx<R> a) {
 template <typename R>
 using nvec2 = R __attribute__((ext_vector_type(2)));
 
-template <typename R>
+template <typename R, bool NTL = true>
 __device__ __forceinline__ cx<R> ld_stream(const cx<R> *p) {
-    if constexpr (TFFT_NT) {
+    if constexpr (TFFT_NT && NTL) {
         const nvec2<R> v = __builtin_nontemporal_load(reinterpret_cast<const nvec2<R> *>(p));
         return {v.x, v.y};
     } else {
@@ -535,21 +535,28 @@ __device__ __forceinline__ void thread_check(cx<R> (&d)[E], const cx<R> (&vin)[E
 // Compile-time shape of a pass kernel.  NTHR = 0: the tile of the dense
 // configuration (cfg_C); NTHR > 0: tiles of NTHR / T signals, so that every
 // variant fills a workgroup of NTHR threads (the persistent ragged kernel).
-template <typename R, int M, int KIND, int FT, int NTHR = 0>
+// TILE: one narrow tile per workgroup (cfg_tile_C signals), nothing kept for
+// a next tile (tile_kernel).  CP is the tile width that defines the checksum
+// group layout, C the one the workgroup holds.
+template <typename R, int M, int KIND, int FT, int NTHR = 0, bool TILE = false>
 struct PassCfg {
     static constexpr int FP64 = sizeof(R) == 8;
     static constexpr bool BLK = FT == FT_BLOCK, SIG = FT == FT_SIGNAL, THR = FT == FT_THREAD;
-    static constexpr bool PF_FENCE = cfg_pf_fence(FP64, M, KIND) != 0;
+    static constexpr bool PF_FENCE = !TILE && cfg_pf_fence(FP64, M, KIND) != 0;
     static constexpr int E = cfg_E(FP64, M, KIND);
     static constexpr int T = M / E;
-    static constexpr int C = NTHR > 0 ? (NTHR / T > 0 ? NTHR / T : 1) : cfg_C(FP64, M, KIND);
+    static constexpr int CP = NTHR > 0 ? (NTHR / T > 0 ? NTHR / T : 1) : cfg_C(FP64, M, KIND);
+    static constexpr int C = TILE ? cfg_tile_C(FP64, M, KIND) : CP;
     static constexpr int NT = C * T;
     // Non-temporal stores, except for tiles whose rows are narrower than a
     // 128-byte line: there the two halves of a line come from different
     // workgroups and must meet in L2 (measured: streaming them wrote up to
     // 26% more bytes than the output holds).
-    static constexpr bool NT_ST = KIND == KIND_ROWS || (C * int(sizeof(R)) * 2 >= TFFT_NT_MIN_ROW &&
-                                                        (KIND == KIND_LAST || TFFT_NT_STRIDED_ST));
+    // (a single tile's data is small enough to be found in the caches by the
+    // next pass or the caller's next kernel: it is not streamed)
+    static constexpr bool NT_LD = !TILE;
+    static constexpr bool NT_ST = !TILE && (KIND == KIND_ROWS || (C * int(sizeof(R)) * 2 >= TFFT_NT_MIN_ROW &&
+                                                        (KIND == KIND_LAST || TFFT_NT_STRIDED_ST)));
     static constexpr bool ENC = BLK || SIG;          // input and output encodings
     static constexpr bool SIGR = SIG && KIND == KIND_ROWS;  // one-sided, tiles of one-signal groups
     static constexpr bool SIGM = SIG && KIND != KIND_ROWS;  // one-sided, per sub-signal of block tiles
@@ -557,29 +564,29 @@ struct PassCfg {
     static constexpr int WAVES = (NT + 63) / 64;
     static constexpr int WIDTH = NT < 64 ? NT : 64;
     // group sums reduced through LDS (see the end of a group)
-    static constexpr bool LDS_RED = TFFT_LDS_RED && NT % 64 == 0 && NT > 64 &&
+    static constexpr bool LDS_RED = !TILE && TFFT_LDS_RED && NT % 64 == 0 && NT > 64 &&
                                     C * M * int(sizeof(R)) * 2 >= 5 * NT * int(sizeof(double));
     // block scheme: a group's decision deferred into the next group, which
     // needs at least one workgroup barrier inside every group
-    static constexpr bool RED_DEFER = TFFT_RED_DEFER && BLK && !LDS_RED && NT % 64 == 0 &&
+    static constexpr bool RED_DEFER = !TILE && TFFT_RED_DEFER && BLK && !LDS_RED && NT % 64 == 0 &&
                                       (NSTAGE >= 2 || KIND == KIND_LAST);
-    static constexpr bool TWREG = cfg_twreg(FP64, M, KIND) != 0;
-    static constexpr bool CREG = ENC && cfg_creg(FP64, M, KIND) != 0;
+    static constexpr bool TWREG = cfg_twreg(FP64, M, KIND) != 0 && !(TILE && M >= 2048);
+    static constexpr bool CREG = !TILE && ENC && cfg_creg(FP64, M, KIND) != 0;
     // prefetch of the next tile straight into a second LDS buffer (16-byte
     // elements, whole wavefronts, both buffers within 128 KiB)
-    static constexpr bool LDSPF = FP64 && (TFFT_LDSPF64 == 2 || (TFFT_LDSPF64 == 1 && KIND == KIND_ROWS)) &&
+    static constexpr bool LDSPF = !TILE && FP64 && (TFFT_LDSPF64 == 2 || (TFFT_LDSPF64 == 1 && KIND == KIND_ROWS)) &&
                                   M >= TFFT_LDSPF64_MIN && C * M * 16 * 2 <= 131072 && NT % 64 == 0;
     static constexpr bool TWLDS = !TWREG && (LDSPF || cfg_twlds(FP64, M, KIND)) && M >= 8;
-    static constexpr bool PREFETCH = !LDSPF && cfg_prefetch(FP64, M, KIND) != 0;
+    static constexpr bool PREFETCH = !TILE && !LDSPF && cfg_prefetch(FP64, M, KIND) != 0;
     static constexpr bool DEFER = cfg_defer(FP64, M, KIND) && (LDSPF || (PREFETCH && PF_FENCE));
 };
 
 // The LDS of one pass kernel variant: the exchange tile, the group-sum
 // slots, the twiddle octant, the prefetch buffer, the one-sided partial sums
 // and the group's first fault.
-template <typename R, int M, int KIND, int FT, int NTHR = 0>
+template <typename R, int M, int KIND, int FT, int NTHR = 0, bool TILE = false>
 struct PassShared {
-    using Cf = PassCfg<R, M, KIND, FT, NTHR>;
+    using Cf = PassCfg<R, M, KIND, FT, NTHR, TILE>;
     alignas(16) cx<R> lds[Cf::C * M];
     double red[Cf::WAVES][5];
     double redg[Cf::RED_DEFER ? 2 : 1][Cf::RED_DEFER ? Cf::WAVES : 1][5];
@@ -618,6 +625,62 @@ __device__ __forceinline__ void vm_wait_all() {
     asm volatile("" ::: "memory");
 }
 
+// A group's decision from its five sums t = {d1, d2, S} (one thread): the
+// threshold test and the quotient that locates the member.  Returns whether
+// the group is flagged, with its record in rc.
+template <int KIND, int CP>
+__device__ __forceinline__ bool decide_group(const PassArgs &a, const double *t, int64_t g, DevRecord &rc) {
+    const double d1r = t[0], d1i = t[1], d2r = t[2], d2i = t[3], S = t[4];
+    const double tau = a.tau_coef * sqrt(S);
+    const double ad1 = sqrt(d1r * d1r + d1i * d1i);
+    if (ad1 <= tau) return false;
+    const double den = d1r * d1r + d1i * d1i;
+    const double rhor = (d2r * d1r + d2i * d1i) / den;
+    const double rhoi = (d2i * d1r - d2r * d1i) / den;
+    int jl = -1;
+    if (isfinite(rhor) && isfinite(rhoi)) {
+        // only members that exist: the last group of a batch may be partial
+        const double fj = floor(rhor + 0.5);
+        if (fj >= 1.0 && fj <= double(group_members<KIND, CP>(a, g))) {
+            const double er = rhor - fj;
+            if (sqrt(er * er + rhoi * rhoi) <= 0.25) jl = int(fj) - 1;
+        }
+    }
+    rc.group = a.g_base + g;
+    rc.pass = a.pass;
+    rc.task = a.task;
+    rc.action = 1;  // detected
+    rc.member = jl;
+    rc.method = jl >= 0 ? 1 : 0;
+    rc.d1r = d1r;
+    rc.d1i = d1i;
+    rc.d2r = d2r;
+    rc.d2i = d2i;
+    rc.tau = tau;
+    rc.s = S;
+    return true;
+}
+
+// Loads and stores coherent over the whole device (other XCDs included).
+template <typename T>
+__device__ __forceinline__ T agent_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void agent_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store(cx<float> *p, cx<float> v) {
+    agent_store(reinterpret_cast<unsigned long long *>(p),
+                (unsigned long long)__float_as_uint(v.im) << 32 | __float_as_uint(v.re));
+}
+// (16 bytes: no atomic store is as wide, so the instruction itself, followed
+// by the wait state that its data registers need before they are rewritten)
+__device__ __forceinline__ void agent_store(cx<double> *p, cx<double> v) {
+    const nvec2<double> w{v.re, v.im};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(w) : "memory");
+}
+
 // Optional per-call hooks of pass_body: `slots` collects the record slots the
 // call appends (the persistent kernel corrects them before it releases the
 // item), at most `slot_cap` of them, counted in *n_slots.
@@ -629,10 +692,15 @@ struct PassHooks {
 
 // The groups g_first, g_first + g_step, ... (< g_end) of one pass, processed
 // by one workgroup of PassCfg::NT threads with the LDS of `sh`.
-template <typename R, int M, int KIND, int FT, int NTHR>
-__device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KIND, FT, NTHR> &sh, cx<R> *nbuf,
-                                          int64_t g_first, int64_t g_end, int64_t g_step, const PassHooks &hk) {
-    using Cf = PassCfg<R, M, KIND, FT, NTHR>;
+// TILE: only the rounds r_first..r_end - 1 of the one group g_first; its part
+// of the five group sums goes to tile_sums (LDS) and nothing is decided.
+// tile_through: the outputs are stored through the caches.
+template <typename R, int M, int KIND, int FT, int NTHR, bool TILE = false>
+__device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KIND, FT, NTHR, TILE> &sh, cx<R> *nbuf,
+                                          int64_t g_first, int64_t g_end, int64_t g_step, const PassHooks &hk,
+                                          int r_first = 0, int r_end = 0, double *tile_sums = nullptr,
+                                          bool tile_through = false) {
+    using Cf = PassCfg<R, M, KIND, FT, NTHR, TILE>;
     constexpr int FP64 = Cf::FP64;
     constexpr bool BLK = Cf::BLK, SIG = Cf::SIG, THR = Cf::THR;
     constexpr bool PF_FENCE = Cf::PF_FENCE;
@@ -643,6 +711,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
     constexpr int E = Cf::E;
     constexpr int T = Cf::T;
     constexpr int C = Cf::C;
+    constexpr int CP = Cf::CP;
     constexpr int NT = Cf::NT;
     using St = Stages<M, E>;
     constexpr int NSTAGE = St::count;
@@ -675,6 +744,15 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
     }
     const cx<R> *in = reinterpret_cast<const cx<R> *>(a.in);
     cx<R> *out = reinterpret_cast<cx<R> *>(a.out);
+    auto store = [&](cx<R> *p, cx<R> v) {
+        if constexpr (TILE && BLK) {
+            if (tile_through) {
+                agent_store(p, v);
+                return;
+            }
+        }
+        st_stream<R, NT_ST>(p, v);
+    };
 
     auto lidx = [](int slot, int pos) -> int { return lds_index<R, M, C, KIND>(slot, pos); };
 
@@ -715,7 +793,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
         else return ldg(stw + t);
     };
     cx<R> tw[TWREG ? St::tw_count() : 1];
-    if constexpr (TWREG) {
+    auto load_tw = [&]() {
         static_for<1, NSTAGE>([&](auto S) {
             constexpr int s = S;
             constexpr int RAD = St::radix(s), NB = St::nb(s);
@@ -723,7 +801,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
                 static_for<1, RAD>([&](auto q) { tw[St::tw_off(s) + p * (RAD - 1) + (q - 1)] = stage_tw(S, p, q); });
             });
         });
-    }
+    };
+    if constexpr (TWREG && !TILE) load_tw();
     cx<double> cc[CREG ? E : 1];
     if constexpr (CREG) {
 #pragma unroll
@@ -735,11 +814,11 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
     const double roti = jr == 0 ? 0.0 : (jr == 1 ? kW3i : -kW3i);
 
     // FT_SIGNAL: a tile of C signals per iteration, each its own group (G = 1)
-    const int rounds = SIGR ? 1 : a.G / C;
+    const int rounds = SIGR ? 1 : (TILE ? r_end : a.G / C);
     const int64_t n_iter = g_end;
     auto mloc = [&](int64_t gg, int rr) -> MemberLoc {
-        if constexpr (SIGR) return member_loc<M, KIND, C>(a, gg * C + c, 0);
-        else return member_loc<M, KIND, C>(a, gg, rr * C + c);
+        if constexpr (SIGR) return member_loc<M, KIND, CP>(a, gg * C + c, 0);
+        else return member_loc<M, KIND, CP>(a, gg, rr * C + c);
     };
     // Software pipeline: the loads of the next tile (next round, or round 0 of
     // this workgroup's next group) are issued before the current tile is
@@ -757,11 +836,11 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
             const uint32_t st = nx_ok ? Ln.in_stride : 0u;
             const uint32_t j0 = nx_ok ? (uint32_t)j : 0u;
 #pragma unroll
-            for (int m = 0; m < E; ++m) nx[m] = ld_stream(s + (j0 + (uint32_t)(T * m)) * st);
+            for (int m = 0; m < E; ++m) nx[m] = ld_stream<R, Cf::NT_LD>(s + (j0 + (uint32_t)(T * m)) * st);
         } else if (nx_ok) {
             const cx<R> *s = in + Ln.in_off;
 #pragma unroll
-            for (int m = 0; m < E; ++m) nx[m] = ld_stream(s + (uint32_t)(j + T * m) * Ln.in_stride);
+            for (int m = 0; m < E; ++m) nx[m] = ld_stream<R, Cf::NT_LD>(s + (uint32_t)(j + T * m) * Ln.in_stride);
         } else {
 #pragma unroll
             for (int m = 0; m < E; ++m) nx[m] = cx<R>{R(0), R(0)};
@@ -894,40 +973,11 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
     };
     // a group's decision from its five sums (one thread)
     auto decide = [&](const double *t, int64_t g) {
-        const double d1r = t[0], d1i = t[1], d2r = t[2], d2i = t[3], S = t[4];
-        const double tau = a.tau_coef * sqrt(S);
-        const double ad1 = sqrt(d1r * d1r + d1i * d1i);
-        if (!(ad1 <= tau)) {
-            const double den = d1r * d1r + d1i * d1i;
-            const double rhor = (d2r * d1r + d2i * d1i) / den;
-            const double rhoi = (d2i * d1r - d2r * d1i) / den;
-            int jl = -1;
-            if (isfinite(rhor) && isfinite(rhoi)) {
-                // only members that exist: the last group of a batch may be partial
-                const double fj = floor(rhor + 0.5);
-                if (fj >= 1.0 && fj <= double(group_members<KIND, C>(a, g))) {
-                    const double er = rhor - fj;
-                    if (sqrt(er * er + rhoi * rhoi) <= 0.25) jl = int(fj) - 1;
-                }
-            }
+        DevRecord rc;
+        if (decide_group<KIND, CP>(a, t, g, rc)) {
             const unsigned long long slot = atomicAdd(&a.rep->n_flag, 1ULL);
             if (hk.slots && *hk.n_slots < hk.slot_cap) hk.slots[(*hk.n_slots)++] = (int64_t)slot;
-            if ((int64_t)slot < a.rec_cap) {
-                DevRecord rc;
-                rc.group = a.g_base + g;
-                rc.pass = a.pass;
-                rc.task = a.task;
-                rc.action = 1;  // detected
-                rc.member = jl;
-                rc.method = jl >= 0 ? 1 : 0;
-                rc.d1r = d1r;
-                rc.d1i = d1i;
-                rc.d2r = d2r;
-                rc.d2i = d2i;
-                rc.tau = tau;
-                rc.s = S;
-                a.recs[slot] = rc;
-            }
+            if ((int64_t)slot < a.rec_cap) a.recs[slot] = rc;
         }
     };
     int64_t g_prev = -1;  // RED_DEFER: the group whose decision is pending
@@ -953,8 +1003,11 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
         }
         double D1r = 0.0, D1i = 0.0, D2r = 0.0, D2i = 0.0;
         double Ssum = 0.0;  // energy of the group's inputs (binary64), for the threshold only
-        for (int r = 0; r < rounds; ++r) {
+        for (int r = TILE ? r_first : 0; r < rounds; ++r) {
             const int b = SIGR ? 0 : r * C + c;
+            // TILE: opaque per round, so that tables and LDS addresses are
+            // formed again for every tile instead of held in registers
+            if constexpr (TILE) asm volatile("" : "+v"(c), "+v"(j));
             const MemberLoc L = mloc(g, r);
             // offsets inside one signal are below N <= 2^24: 32-bit arithmetic
             cx<R> *dst = out + L.out_off;
@@ -969,6 +1022,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
 #pragma unroll
                 for (int m = 0; m < E; ++m) cl[m] = ldg(cv + j + T * m);
             }
+            if constexpr (TILE && TWREG) load_tw();
             cx<double> twA{1.0, 0.0}, twB{1.0, 0.0};
             if constexpr (KIND == KIND_STRIDED) {
                 // w_L^{k i} = w_N^{k i N/L}; N is a power of two, so the
@@ -1204,7 +1258,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
                 } else if (L.valid) {
 #pragma unroll
                     for (int m = 0; m < E; ++m)
-                        st_stream<R, NT_ST>(base + (uint32_t)(j2 + T * m) * ostr, lds[lidx(c2, j2 + T * m)]);
+                        store(base + (uint32_t)(j2 + T * m) * ostr, lds[lidx(c2, j2 + T * m)]);
                 }
                 tile_sync();
             } else if constexpr (DEFER) {
@@ -1216,7 +1270,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
             } else {
                 if (L.valid) {
 #pragma unroll
-                    for (int m = 0; m < E; ++m) st_stream<R, NT_ST>(dst + (uint32_t)(j + T * m) * ostr, d[m]);
+                    for (int m = 0; m < E; ++m) store(dst + (uint32_t)(j + T * m) * ostr, d[m]);
                 }
             }
             if constexpr (SIGM) {
@@ -1227,7 +1281,21 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
         }  // rounds
 
         if constexpr (SIGR) member_check(gsig, 0, gsig < a.n_groups, D1r, D1i, Ssum, 1);
-        if constexpr (BLK) {
+        if constexpr (TILE && BLK) {
+            double v[5] = {D1r, D1i, D2r, D2i, Ssum};
+#pragma unroll
+            for (int q = 0; q < 5; ++q) v[q] = wave_sum_dpp(v[q], Dpp64{});
+            if ((tid & 63) == 63) {
+#pragma unroll
+                for (int q = 0; q < 5; ++q) red[tid >> 6][q] = v[q];
+            }
+            tile_sync();
+            if (tid < 5) {
+                double s = 0.0;
+                for (int w = 0; w < WAVES; ++w) s += red[w][tid];
+                tile_sums[tid] = s;
+            }
+        } else if constexpr (BLK) {
             if constexpr (LDS_RED) {
                 // partial sums through the (now idle) exchange buffer, added
                 // up by one wavefront: each thread stores five values instead
@@ -1557,7 +1625,106 @@ __global__ void __launch_bounds__(kCorrThreads) correct_kernel(PassArgs a) {
         correct_record<R, M, KIND, C, kCorrThreads>(a, i, buf, scratch);
 }
 
+// ------------------------------------------------------------- tile kernel
+// Launches that leave the chip idle at one workgroup per checksum group: a
+// group's tiles (cfg_tile_C signals or sub-signals each) are split over
+// several workgroups.  Their partial sums go to memory, and the workgroup that
+// takes the group's last ticket adds them up in order of the parts (so the
+// residuals do not depend on the order of arrival), decides and corrects.
+// Its correction reads outputs of the other parts, so a group of several
+// parts stores its outputs through the caches (a release fence per workgroup
+// instead writes the XCD's whole L2 back: complex64 N = 1024, 2^20 elements
+// 45 us, through the caches 9).  State and record of a group have a place of
+// their own: nothing is counted, so nothing is reset between executions, and
+// one launch per pass does everything.
+template <typename R, int M, int KIND, int FT>
+__global__ void __launch_bounds__(cfg_tile_threads(sizeof(R) == 8, M, KIND)) tile_kernel(PassArgs a, TileArgs t) {
+    using Cf = PassCfg<R, M, KIND, FT, 0, true>;
+    using Shared = PassShared<R, M, KIND, FT, 0, true>;
+    static_assert(Cf::NT % 64 == 0 && (KIND == KIND_ROWS || Cf::CP % Cf::C == 0), "tile kernel shape");
+    constexpr size_t CORR = FT == FT_BLOCK ? sizeof(cx<double>) * M : 1;  // the correction's binary64 transform
+    __shared__ __align__(16) unsigned char pool[sizeof(Shared) > CORR ? sizeof(Shared) : CORR];
+    __shared__ double scratch[Cf::NT / 64];
+    __shared__ double sums[5];
+    __shared__ int flagged;
+    const int tid = threadIdx.x;
+    // consecutive workgroups run on different XCDs: each XCD takes a
+    // contiguous range of tiles (the grid is padded to a multiple of 8)
+    const int64_t w = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (w >= a.n_groups << t.split_log2) return;
+    const int64_t g = w >> t.split_log2;
+    const int r = (int)(w & ((1 << t.split_log2) - 1));  // this workgroup's part of the group
+    const bool split = t.split_log2 > 0;
+    pass_body<R, M, KIND, FT, 0, true>(a, *reinterpret_cast<Shared *>(pool), nullptr, g, g + 1, 1,
+                                       PassHooks{nullptr, nullptr, 0}, r * t.rounds, (r + 1) * t.rounds, sums,
+                                       split && t.fix);
+    if constexpr (FT == FT_NONE) {
+        if (r == 0 && tid == 0) t.state[g] = 0;
+    } else {
+        if (split && t.fix) vm_wait_all();  // every wavefront's outputs before the ticket
+        __syncthreads();
+        if (tid < 64) {
+            const unsigned parts = 1u << t.split_log2;
+            bool last = true;
+            double s[5];
+#pragma unroll
+            for (int q = 0; q < 5; ++q) s[q] = sums[q];
+            if (split) {
+                double *part = t.part + (g << t.split_log2) * 5;
+                if (tid < 5) agent_store(part + r * 5 + tid, sums[tid]);
+                vm_wait_all();  // the sums before the ticket
+                unsigned old = 0;
+                if (tid == 0) old = atomicInc(t.tick + g * kTickStride, parts - 1);
+                last = __builtin_amdgcn_readfirstlane(old) == parts - 1;
+                if (last) {
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) s[q] = tid < (int)parts ? agent_load(part + tid * 5 + q) : 0.0;
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) s[q] = wave_sum(s[q], 64);
+                }
+            }
+            if (tid == 0) {
+                int bad = 0;
+                if (last) {
+                    DevRecord rc;
+                    bad = decide_group<KIND, Cf::CP>(a, s, g, rc);
+                    if (bad) a.recs[t.rec0 + g] = rc;
+                    t.state[g] = bad;
+                }
+                flagged = bad;
+            }
+        }
+        if (!t.fix) return;
+        __syncthreads();
+        if (flagged) {
+            if (split) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            correct_record<R, M, KIND, Cf::CP, Cf::NT>(a, t.rec0 + g, reinterpret_cast<cx<double> *>(pool), scratch);
+        }
+    }
+}
+
 // ------------------------------------------------------------- dispatch
+template <typename R, int M, int KIND>
+static hipError_t launch_tile_one(int ft, const PassArgs &a, const TileArgs &t, hipStream_t st) {
+    constexpr int NT = cfg_tile_threads(sizeof(R) == 8, M, KIND);
+    const dim3 grid((unsigned)(((a.n_groups << t.split_log2) + 7) / 8 * 8));
+    if (ft == FT_BLOCK) hipLaunchKernelGGL((tile_kernel<R, M, KIND, FT_BLOCK>), grid, dim3(NT), 0, st, a, t);
+    else hipLaunchKernelGGL((tile_kernel<R, M, KIND, FT_NONE>), grid, dim3(NT), 0, st, a, t);
+    return hipGetLastError();
+}
+
+template <typename R, int M>
+hipError_t tile_m(int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st) {
+    if constexpr (M <= 4096) {
+        if (kind == KIND_ROWS) return launch_tile_one<R, M, KIND_ROWS>(ft, a, t, st);
+    }
+    if constexpr (M >= 16 && M <= 1024) {
+        if (kind == KIND_STRIDED) return launch_tile_one<R, M, KIND_STRIDED>(ft, a, t, st);
+        if (kind == KIND_LAST) return launch_tile_one<R, M, KIND_LAST>(ft, a, t, st);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <typename R, int M, int KIND, int FT>
 static hipError_t launch_one(const PassArgs &a, int grid, hipStream_t st) {
     constexpr int NT = cfg_threads(sizeof(R) == 8, M, KIND);
@@ -1632,10 +1799,12 @@ int occ_m(int kind, int ft) {
 #define TFFT_INSTANTIATE_M(R, M)                                                         \
     template hipError_t launch_m<R, M>(int, int, const PassArgs &, int, hipStream_t); \
     template hipError_t correct_m<R, M>(int, const PassArgs &, int, hipStream_t);     \
+    template hipError_t tile_m<R, M>(int, int, const PassArgs &, const TileArgs &, hipStream_t); \
     template int occ_m<R, M>(int, int);
 #define TFFT_EXTERN_M(R, M)                                                                     \
     extern template hipError_t launch_m<R, M>(int, int, const PassArgs &, int, hipStream_t); \
     extern template hipError_t correct_m<R, M>(int, const PassArgs &, int, hipStream_t);     \
+    extern template hipError_t tile_m<R, M>(int, int, const PassArgs &, const TileArgs &, hipStream_t); \
     extern template int occ_m<R, M>(int, int);
 #define TFFT_FOR_EACH_M(X, R) X(R, 2) X(R, 4) X(R, 8) X(R, 16) X(R, 32) X(R, 64) X(R, 128) X(R, 256) \
     X(R, 512) X(R, 1024) X(R, 2048) X(R, 4096) X(R, 8192)

@@ -54,6 +54,11 @@ hipError_t launch_correct(int fp64, int M, int kind, const PassArgs &a, int grid
     return by_m<float>(M, [&](auto m) { return correct_m<float, decltype(m)::value>(kind, a, grid, st); });
 }
 
+hipError_t launch_tile(int fp64, int M, int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st) {
+    if (fp64) return by_m<double>(M, [&](auto m) { return tile_m<double, decltype(m)::value>(kind, ft, a, t, st); });
+    return by_m<float>(M, [&](auto m) { return tile_m<float, decltype(m)::value>(kind, ft, a, t, st); });
+}
+
 int pass_occupancy(int fp64, int M, int kind, int ft) {
     int r = 0;
     auto f = [&](auto m) {

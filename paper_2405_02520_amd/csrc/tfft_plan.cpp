@@ -75,6 +75,7 @@ struct PassPlan {
     int32_t *d_fault_head = nullptr;
     DevFault *d_faults = nullptr;
     double tau_coef = 0.0;
+    TileArgs tile{};             // tile launches (everything but the mode)
 };
 
 }  // namespace
@@ -110,6 +111,8 @@ struct tfft_plan_s {
     int launched_correct = 0;
     int64_t chunk = 0;           // multi-pass plans: signals per chunk of the batch (= batch: no chunking)
     int persistent = 0;          // shaped for the persistent ragged kernel (tiles of 512 threads)
+    int tile = 0;                // runs as tile launches (use_tiles)
+    void *d_tile = nullptr;      // tile launches, one allocation: tickets and states, partial sums
 };
 
 namespace {
@@ -282,6 +285,7 @@ void free_plan(tfft_plan_s *p) {
     (void)hipFree(p->d_rep);
     (void)hipFree(p->d_recs);
     (void)hipFree(p->d_sig_off);
+    (void)hipFree(p->d_tile);
     for (auto &e : p->ev)
         if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(cur);
@@ -414,6 +418,59 @@ PassArgs pass_args(const tfft_plan_s *p, int i, const ChunkGeom &cg, int64_t nb,
     return A;
 }
 
+// Tiles per checksum group of pass P in a tile launch, or 0 where the group is
+// not a whole number of tiles.
+int tile_rounds(const tfft_plan_s *p, const PassPlan &P) {
+    const int c = cfg_tile_C(p->dtype == TFFT_C128, P.M, P.kind);
+    return P.G % c == 0 ? P.G / c : 0;
+}
+
+// log2 of the workgroups that share a group: the largest power of two that
+// divides its tiles (a group need not have a power of two of them: a batch of
+// 3 signals gives groups of 48 members), less where the launch then has more
+// than TFFT_TILE_WAVES wavefronts.
+int tile_split_log2(const tfft_plan_s *p, const PassPlan &P) {
+    const int fp64 = p->dtype == TFFT_C128;
+    int k = __builtin_ctz((unsigned)tile_rounds(p, P));
+    const int64_t waves = cfg_tile_threads(fp64, P.M, P.kind) / 64;
+    while (k > 0 && (P.n_groups << k) * waves > TFFT_TILE_WAVES) --k;
+    return k;
+}
+
+// Whether a plan runs as tile launches.  A pass kernel has one workgroup per
+// checksum group, so a batch of few groups leaves most of the chip idle; its
+// tiles, spread over the chip, take over where every pass's launch would hold
+// few wavefronts.  Measured (us per call, pass kernels then tiles; FT CORRECT /
+// OFF): complex64 N = 256 at 2^14 elements (4 wavefronts) 18 -> 6 / 15 -> 3.5;
+// N = 1024 at 2^20 (64) 78 -> 11 / 70 -> 8, at 2^23 (512) 86 -> 45 / 78 -> 35,
+// at 2^24 (1024) 93 -> 98 / 87 -> 81; N = 2^14 at 2^20 (1024) 27 -> 19 / 19 ->
+// 13; N = 2^16 at 2^21 (1024) 40 -> 33 / 30 -> 20, at 2^22 (2048) 44 -> 56 /
+// 35 -> 33; complex128 N = 4096 at 2^23 (1024) 126 -> 87 / 158 -> 66: the line
+// lies at 1024 wavefronts.  It lies lower where the tile kernel holds one
+// 512-thread workgroup per CU but the pass kernel streams well: complex64 rows
+// of 4096 points (at 512 wavefronts 52 -> 39 / 47 -> 24, at 1024 55 -> 67 /
+// 49 -> 43) and strided passes of 1024 (complex128 N = 2^20 at 128 wavefronts
+// 44 -> 36 / 38 -> 32, at 512 83 -> 106 / 80 -> 73).  Signals of up to 16 points
+// always run as tiles: their pass kernels hold less than a wavefront per
+// workgroup (complex64 N = 16 at 2^24 154 -> 85 / 146 -> 79).  A plan with a
+// grid_scale or a chunk of its own keeps the pass kernels those describe.
+bool use_tiles(const tfft_plan_s *p, int grid_scale) {
+    if (p->persistent || p->scheme != TFFT_SCHEME_BLOCK || grid_scale != 0 || p->chunk < p->batch) return false;
+    const int fp64 = p->dtype == TFFT_C128;
+    bool few = true, small = true;
+    for (int i = 0; i < p->passes; ++i) {
+        const PassPlan &P = p->pass[i];
+        if (tile_rounds(p, P) < 1) return false;
+        const int threads = cfg_threads(fp64, P.M, P.kind);
+        int64_t limit = TFFT_TILE_MAX_WAVES;
+        if (P.kind == KIND_ROWS && P.M >= 4096 && !fp64) limit /= 2;
+        if (P.kind == KIND_STRIDED && P.M >= 1024) limit /= 4;
+        small = small && threads < 64;
+        few = few && P.n_groups * ((threads + 63) / 64) <= limit;
+    }
+    return small || few;
+}
+
 // Device buffers of one execution: the report counters, the records and the
 // multi-pass workspace (the plan's own, or parts of the static scratch).
 struct ExecBufs {
@@ -447,7 +504,8 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
     hipStream_t st = (hipStream_t)stream;
     const int fp64 = p->dtype == TFFT_C128;
     const int ft = mode != TFFT_FT_OFF;
-    if (launch_reset(rep, st) != hipSuccess) return TFFT_E_HIP;
+    const bool tile = p->tile != 0;
+    if (!tile && launch_reset(rep, st) != hipSuccess) return TFFT_E_HIP;
     // one chunk (the whole batch) unless the plan chunks its multi-pass batch
     const int64_t chunk = (p->passes > 1 && p->chunk > 0) ? p->chunk : p->batch;
     const bool timed = p->timing != 0;
@@ -456,7 +514,8 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
     const int scheme_ft = !ft ? FT_NONE
                               : (p->scheme == TFFT_SCHEME_SIGNAL ? FT_SIGNAL
                                                                  : (p->scheme == TFFT_SCHEME_THREAD ? FT_THREAD : FT_BLOCK));
-    const bool correct = mode == TFFT_FT_CORRECT && p->scheme != TFFT_SCHEME_THREAD;
+    // (a tile launch corrects its own groups)
+    const bool correct = mode == TFFT_FT_CORRECT && p->scheme != TFFT_SCHEME_THREAD && !tile;
     for (int64_t c0 = 0; c0 < p->batch; c0 += chunk) {
         const int64_t nb = std::min(chunk, p->batch - c0);
         // the caller's buffers from signal c0 on (dense: an offset pointer;
@@ -469,7 +528,13 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
             const PassPlan &P = p->pass[i];
             const ChunkGeom cg = chunk_geom(p, P, c0, nb);
             const PassArgs A = pass_args(p, i, cg, nb, cin, cout, work, sig, inverse, mode, rep, recs);
-            if (launch_pass(fp64, P.M, P.kind, scheme_ft, A, cg.grid, st) != hipSuccess) return TFFT_E_HIP;
+            if (tile) {
+                TileArgs T = P.tile;
+                T.fix = mode == TFFT_FT_CORRECT;
+                if (launch_tile(fp64, P.M, P.kind, scheme_ft, A, T, st) != hipSuccess) return TFFT_E_HIP;
+            } else if (launch_pass(fp64, P.M, P.kind, scheme_ft, A, cg.grid, st) != hipSuccess) {
+                return TFFT_E_HIP;
+            }
             if (per_pass_events && hipEventRecord(p->ev[1 + 2 * i], st) != hipSuccess) return TFFT_E_HIP;
             if (correct) {
                 // one workgroup per possible record, at most TFFT_CORRECT_GRID; a workgroup
@@ -611,6 +676,40 @@ int shape_plan(tfft_plan_s *p, int64_t n, int64_t batch, int dtype, const tfft_o
     return TFFT_OK;
 }
 
+// The tile launches' memory: the tickets (shared by the passes, which run one
+// after the other, and zero between launches), every pass's group states, the
+// partial sums (shared as well).
+int tile_buffers(tfft_plan_s *p) {
+    int64_t parts = 0, groups = 0, all = 0;
+    for (int i = 0; i < p->passes; ++i) {
+        PassPlan &P = p->pass[i];
+        P.tile.split_log2 = tile_split_log2(p, P);
+        P.tile.rounds = tile_rounds(p, P) >> P.tile.split_log2;
+        P.tile.rec0 = all;
+        parts = std::max(parts, P.n_groups << P.tile.split_log2);
+        if (P.tile.split_log2 > 0) groups = std::max(groups, P.n_groups);
+        all += P.n_groups;
+    }
+    const size_t tick_bytes = sizeof(uint32_t) * kTickStride * (size_t)groups;
+    const size_t state_bytes = (sizeof(int32_t) * (size_t)all + 255) / 256 * 256;
+    if (hipMalloc(&p->d_tile, tick_bytes + state_bytes + sizeof(double) * 5 * (size_t)parts) != hipSuccess) {
+        p->d_tile = nullptr;
+        return TFFT_E_NOMEM;
+    }
+    // (a copy, unlike a memset, is complete when it returns: the first
+    // execution may be on a stream that does not wait for the null stream)
+    const std::vector<char> zero(tick_bytes + state_bytes, 0);
+    if (hipMemcpy(p->d_tile, zero.data(), zero.size(), hipMemcpyHostToDevice) != hipSuccess) return TFFT_E_HIP;
+    char *base = static_cast<char *>(p->d_tile);
+    for (int i = 0; i < p->passes; ++i) {
+        TileArgs &T = p->pass[i].tile;
+        T.tick = reinterpret_cast<uint32_t *>(base);
+        T.state = reinterpret_cast<int32_t *>(base + tick_bytes) + T.rec0;
+        T.part = reinterpret_cast<double *>(base + tick_bytes + state_bytes);
+    }
+    return TFFT_OK;
+}
+
 // Plan construction shared by dense and ragged plans.  host_off (may be
 // NULL): element offsets of the `batch` signals inside buffers spanning
 // `extent` elements.
@@ -658,6 +757,8 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
         else if (hipMemset(p->d_rep, 0, sizeof(DevReport)) != hipSuccess)
             rc = TFFT_E_HIP;
     }
+    p->tile = use_tiles(p, opt ? opt->grid_scale : 0);
+    if (rc == TFFT_OK && p->tile) rc = tile_buffers(p);
     if (rc == TFFT_OK && host_off) {
         std::vector<int64_t> off(host_off, host_off + batch);
         rc = upload(&p->d_sig_off, off);
@@ -667,6 +768,35 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
         return rc;
     }
     *out = p;
+    return TFFT_OK;
+}
+
+// The report of an execution as tile launches: the flagged groups' records
+// and the counters they add up to.
+int read_tile_report(const tfft_plan_s *p, DevReport *h, std::vector<DevRecord> *recs) {
+    *h = DevReport{};
+    const TileArgs &last = p->pass[p->passes - 1].tile;
+    const size_t all = (size_t)(last.rec0 + p->pass[p->passes - 1].n_groups);
+    std::vector<int32_t> state(all);
+    if (hipMemcpy(state.data(), p->pass[0].tile.state, sizeof(int32_t) * all, hipMemcpyDeviceToHost) != hipSuccess)
+        return TFFT_E_HIP;
+    // consecutive flagged groups in one copy
+    for (size_t i = 0; i < all; ++i) {
+        if (!state[i]) continue;
+        size_t e = i + 1;
+        while (e < all && state[e]) ++e;
+        const size_t at = recs->size();
+        recs->resize(at + (e - i));
+        if (hipMemcpy(recs->data() + at, p->recs_last + i, sizeof(DevRecord) * (e - i), hipMemcpyDeviceToHost) != hipSuccess)
+            return TFFT_E_HIP;
+        i = e;
+    }
+    h->n_flag = recs->size();
+    for (const DevRecord &r : *recs) {
+        h->corrected += r.action == TFFT_ACT_CORRECTED;
+        h->benign += r.action == TFFT_ACT_BENIGN;
+        h->uncorrectable += r.action == TFFT_ACT_UNCORRECTABLE;
+    }
     return TFFT_OK;
 }
 
@@ -761,12 +891,17 @@ int tfft_get_report(tfft_plan p, tfft_counts *counts, tfft_record *recs, int64_t
     Guard guard(p->device);
     if (hipStreamSynchronize(p->last_stream) != hipSuccess) return TFFT_E_HIP;
     DevReport h;
-    if (hipMemcpy(&h, p->rep_last, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess) return TFFT_E_HIP;
-    const int64_t nrec = std::min<int64_t>((int64_t)h.n_flag, p->rec_cap);
-    std::vector<DevRecord> dr((size_t)nrec);
-    if (nrec > 0 &&
-        hipMemcpy(dr.data(), p->recs_last, sizeof(DevRecord) * (size_t)nrec, hipMemcpyDeviceToHost) != hipSuccess)
-        return TFFT_E_HIP;
+    std::vector<DevRecord> dr;
+    if (p->tile) {
+        if (read_tile_report(p, &h, &dr) != TFFT_OK) return TFFT_E_HIP;
+    } else {
+        if (hipMemcpy(&h, p->rep_last, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess) return TFFT_E_HIP;
+        dr.resize((size_t)std::min<int64_t>((int64_t)h.n_flag, p->rec_cap));
+        if (!dr.empty() &&
+            hipMemcpy(dr.data(), p->recs_last, sizeof(DevRecord) * dr.size(), hipMemcpyDeviceToHost) != hipSuccess)
+            return TFFT_E_HIP;
+    }
+    const int64_t nrec = (int64_t)dr.size();
     int64_t groups = 0;
     if (p->last_mode != TFFT_FT_OFF)
         for (int i = 0; i < p->passes; ++i)  // one-sided: every (sub-)signal is checked
