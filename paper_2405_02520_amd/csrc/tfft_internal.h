@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace tfft {
@@ -90,6 +91,16 @@ constexpr int cfg_C(int fp64, int M, int kind) {
     const int maxthr = kind == KIND_ROWS ? 256 : (fp64 ? TFFT_MP_THREADS64 : TFFT_MP_THREADS32);
     while (c > 1 && (c * T > maxthr || c * M * S > 65536)) c /= 2;
     return c < 1 ? 1 : c;
+}
+// Adjacent sub-signals per strip of the checksum group layout of a multi-pass
+// pass: the tile width, except that complex64 plans with whole groups of 64
+// take the wider strips of the column kernels (tfft_cols.h), whose rows of
+// 256 bytes (128 for M = 512) set the bandwidth of the strided loads and the
+// transposed stores.  cfg_CP: 0 where the plan chooses between the two.
+constexpr bool cfg_cols(int fp64, int M, int kind) { return !fp64 && kind != KIND_ROWS && M >= 64 && M <= 512; }
+constexpr int cfg_wide_C(int M) { return M <= 256 ? 32 : 16; }
+constexpr int cfg_CP(int fp64, int M, int kind) {
+    return cfg_cols(fp64, M, kind) && cfg_wide_C(M) > cfg_C(fp64, M, kind) ? 0 : cfg_C(fp64, M, kind);
 }
 // Keep the stage twiddles / the checksum vector of a thread in registers
 // across the signals it processes (1), or re-read them from the L1/L2
@@ -296,6 +307,16 @@ constexpr int cfg_tile_threads(int fp64, int M, int kind) {
     return cfg_tile_C(fp64, M, kind) * (M / cfg_E(fp64, M, kind));
 }
 
+// Column kernels (tfft_cols.h): threads of a workgroup, one lane per member
+// of a 64-member group.
+constexpr int cfg_col_threads(int M) { return (M / 8 < 16 ? M / 8 : 16) * 64; }
+// Workgroups of a column kernel's launch: one per CU (two of the 512-thread
+// ones), each of which walks its share of the groups with the next tile's loads
+// in flight (measured: 1024 are 0-5% slower, every restart drains the loads).
+#ifndef TFFT_COL_GRID
+#define TFFT_COL_GRID 256
+#endif
+
 // Radix sequence: as many stages of radix E as fit, then one stage of the
 // remaining factor (which divides E).
 constexpr int n_full(int M, int E) { return E <= 1 ? 0 : ilog2c(M) / ilog2c(E); }
@@ -310,6 +331,22 @@ struct DevRecord {
     int32_t task, pad_;  // persistent ragged kernel: the (class, pass) task; 0 otherwise
     double d1r, d1i, d2r, d2i, tau, s;
 };
+
+// Member of a record whose location is still to be derived from its sums
+// (column kernels): by the correction, or by the host that reads the report.
+constexpr int kUnlocated = -2;
+// The member (of `members`) that the quotient d2 / d1 of the residuals points
+// at, within a quarter of its one-based number, or -1.
+__host__ __device__ inline int quotient_member(double d1r, double d1i, double d2r, double d2i, int members) {
+    const double den = d1r * d1r + d1i * d1i;
+    const double rhor = (d2r * d1r + d2i * d1i) / den;
+    const double rhoi = (d2i * d1r - d2r * d1i) / den;
+    // (comparisons that an infinity or a NaN fails)
+    if (!(fabs(rhor) <= 1e6 && fabs(rhoi) <= 0.25)) return -1;
+    const double fj = floor(rhor + 0.5);
+    const double er = rhor - fj;
+    return fj >= 1.0 && fj <= double(members) && sqrt(er * er + rhoi * rhoi) <= 0.25 ? int(fj) - 1 : -1;
+}
 
 struct DevReport {
     unsigned long long n_flag;         // flagged groups (record slots requested)
@@ -371,7 +408,7 @@ struct PassArgs {
     int32_t task;       // persistent ragged kernel: task index carried by the records (0 otherwise)
     int32_t ns_log2;    // multi-pass: log2(n_strips)
     int32_t o_log2;     // STRIDED: log2(O)
-    int32_t pad_;
+    int32_t c_log2;     // multi-pass: log2 of the sub-signals per strip
 };
 
 // What a tile launch needs besides PassArgs: a group's tiles are split over
@@ -440,6 +477,7 @@ void *scratch_address(int device);
 // Host-side launchers (defined in the kernel translation unit).
 hipError_t launch_pass(int fp64, int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st);
 hipError_t launch_correct(int fp64, int M, int kind, const PassArgs &a, int grid, hipStream_t st);
+hipError_t launch_cols(int fp64, int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st);
 hipError_t launch_tile(int fp64, int M, int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st);
 hipError_t launch_reset(DevReport *rep, hipStream_t st);
 // Persistent ragged kernel: launch over `grid` workgroups, its resident

@@ -174,7 +174,8 @@ struct Stages {
 
 // ----------------------------------------------------------- addressing
 // Where member b of group g lives.  Offsets inside one signal are below
-// N <= 2^24, so the in-signal part is 32-bit.
+// N <= 2^24, so the in-signal part is 32-bit.  C: sub-signals per strip of the
+// group layout, or 0 where the plan chooses it (a.c_log2; cfg_CP).
 struct MemberLoc {
     int64_t in_off, out_off;
     uint32_t in_stride, out_stride;
@@ -198,8 +199,15 @@ __device__ __forceinline__ MemberLoc member_loc(const PassArgs &a, int64_t g, in
         // n_strips and O are powers of two: shifts and masks (TFFT_MEMBER_SHIFT)
         // or divisions
         const int64_t strip = TFFT_MEMBER_SHIFT ? (g & (a.n_strips - 1)) : g % a.n_strips;
-        const int64_t u = (TFFT_MEMBER_SHIFT ? (g >> a.ns_log2) : g / a.n_strips) * a.rb + b / C;  // outer unit
-        const int64_t r = strip * C + b % C;                 // sub-signal inside the unit
+        int64_t u = (TFFT_MEMBER_SHIFT ? (g >> a.ns_log2) : g / a.n_strips) * a.rb;  // outer unit
+        int64_t r;                                                                   // sub-signal inside the unit
+        if constexpr (C > 0) {
+            u += b / C;
+            r = strip * C + b % C;
+        } else {
+            u += b >> a.c_log2;
+            r = (strip << a.c_log2) + (b & ((1 << a.c_log2) - 1));
+        }
         L.valid = u < a.n_outer;
         if constexpr (KIND == KIND_STRIDED) {
             const int64_t beta = L.valid ? (TFFT_MEMBER_SHIFT ? (u >> a.o_log2) : u / a.O) : 0;
@@ -231,7 +239,7 @@ __device__ __forceinline__ int group_members(const PassArgs &a, int64_t g) {
         return left < a.G ? (int)left : a.G;
     } else {
         const int64_t left = a.n_outer - (g / a.n_strips) * a.rb;
-        return C * (left < a.rb ? (int)left : a.rb);
+        return (C > 0 ? C : 1 << a.c_log2) * (left < a.rb ? (int)left : a.rb);
     }
 }
 
@@ -253,7 +261,8 @@ __device__ __forceinline__ int lds_index(int slot, int pos) {
 }
 
 // w_N^t from the two-level fp64 table.
-__device__ __forceinline__ cx<double> itw(const PassArgs &a, int64_t t) {
+template <typename Args>
+__device__ __forceinline__ cx<double> itw(const Args &a, int64_t t) {
     const int64_t mask = (int64_t(1) << a.itw_bits) - 1;
     const cx<double> lo = ldg(reinterpret_cast<const cx<double> *>(a.itw_lo) + (t & mask));
     const cx<double> hi = ldg(reinterpret_cast<const cx<double> *>(a.itw_hi) + (t >> a.itw_bits));
@@ -536,8 +545,8 @@ __device__ __forceinline__ void thread_check(cx<R> (&d)[E], const cx<R> (&vin)[E
 // configuration (cfg_C); NTHR > 0: tiles of NTHR / T signals, so that every
 // variant fills a workgroup of NTHR threads (the persistent ragged kernel).
 // TILE: one narrow tile per workgroup (cfg_tile_C signals), nothing kept for
-// a next tile (tile_kernel).  CP is the tile width that defines the checksum
-// group layout, C the one the workgroup holds.
+// a next tile (tile_kernel).  CP is the strip width of the checksum group
+// layout (0: the plan's), C the width of the tile that the workgroup holds.
 template <typename R, int M, int KIND, int FT, int NTHR = 0, bool TILE = false>
 struct PassCfg {
     static constexpr int FP64 = sizeof(R) == 8;
@@ -545,8 +554,9 @@ struct PassCfg {
     static constexpr bool PF_FENCE = !TILE && cfg_pf_fence(FP64, M, KIND) != 0;
     static constexpr int E = cfg_E(FP64, M, KIND);
     static constexpr int T = M / E;
-    static constexpr int CP = NTHR > 0 ? (NTHR / T > 0 ? NTHR / T : 1) : cfg_C(FP64, M, KIND);
-    static constexpr int C = TILE ? cfg_tile_C(FP64, M, KIND) : CP;
+    static constexpr int CN = NTHR > 0 ? (NTHR / T > 0 ? NTHR / T : 1) : cfg_C(FP64, M, KIND);
+    static constexpr int CP = NTHR > 0 ? CN : cfg_CP(FP64, M, KIND);
+    static constexpr int C = TILE ? cfg_tile_C(FP64, M, KIND) : CN;
     static constexpr int NT = C * T;
     // Non-temporal stores, except for tiles whose rows are narrower than a
     // 128-byte line: there the two halves of a line come from different
@@ -634,18 +644,8 @@ __device__ __forceinline__ bool decide_group(const PassArgs &a, const double *t,
     const double tau = a.tau_coef * sqrt(S);
     const double ad1 = sqrt(d1r * d1r + d1i * d1i);
     if (ad1 <= tau) return false;
-    const double den = d1r * d1r + d1i * d1i;
-    const double rhor = (d2r * d1r + d2i * d1i) / den;
-    const double rhoi = (d2i * d1r - d2r * d1i) / den;
-    int jl = -1;
-    if (isfinite(rhor) && isfinite(rhoi)) {
-        // only members that exist: the last group of a batch may be partial
-        const double fj = floor(rhor + 0.5);
-        if (fj >= 1.0 && fj <= double(group_members<KIND, CP>(a, g))) {
-            const double er = rhor - fj;
-            if (sqrt(er * er + rhoi * rhoi) <= 0.25) jl = int(fj) - 1;
-        }
-    }
+    // only members that exist: the last group of a batch may be partial
+    const int jl = quotient_member(d1r, d1i, d2r, d2i, group_members<KIND, CP>(a, g));
     rc.group = a.g_base + g;
     rc.pass = a.pass;
     rc.task = a.task;
@@ -1409,8 +1409,8 @@ __device__ __forceinline__ double block_sum(double v, double *scratch) {
 }
 
 // Correction of record i (a flagged group of the pass described by `a`) by
-// one workgroup of NTH threads, with C the tile width of the pass kernel that
-// defined the group layout; `buf` holds M binary64 values, `scratch` NTH / 64
+// one workgroup of NTH threads, with C the strip width of the group layout (0:
+// the plan's); `buf` holds M binary64 values, `scratch` NTH / 64
 // doubles (LDS).  Records of another pass, task or chunk, or already acted
 // on, are skipped.
 template <typename R, int M, int KIND, int C, int NTH>
@@ -1423,7 +1423,7 @@ __device__ __forceinline__ void correct_record(const PassArgs &a, int64_t i, cx<
     const cx<double> *cv = reinterpret_cast<const cx<double> *>(a.cvec);
     const cx<double> *w64 = reinterpret_cast<const cx<double> *>(a.stw64);
     {
-        const DevRecord rec = a.recs[i];
+        DevRecord rec = a.recs[i];
         // records of this pass and of this launch's groups (a chunk of the
         // batch covers groups g_base .. g_base + n_groups - 1)
         if (rec.pass != a.pass || rec.task != a.task || rec.action != 1) return;
@@ -1454,6 +1454,8 @@ __device__ __forceinline__ void correct_record(const PassArgs &a, int64_t i, cx<
         };
 
         // location: quotient of the residuals, else per-signal residuals
+        if (rec.member == kUnlocated)
+            rec.member = quotient_member(rec.d1r, rec.d1i, rec.d2r, rec.d2i, group_members<KIND, C>(a, g));
         int jl = rec.member;
         if (jl >= a.G || (jl >= 0 && !member_loc<M, KIND, C>(a, g, jl).valid)) jl = -1;
         int method = rec.method == 4 ? 4 : (jl >= 0 ? 1 : 0);
@@ -1496,7 +1498,7 @@ __device__ __forceinline__ void correct_record(const PassArgs &a, int64_t i, cx<
         // tile when those are adjacent in memory (strided passes; outputs of
         // the last pass), else along the positions; the C lanes that share a
         // position are then summed with lane shuffles.
-        constexpr int CL = (KIND == KIND_ROWS) ? 1 : C;
+        constexpr int CL = (KIND == KIND_ROWS) ? 1 : (C > 0 ? C : cfg_C(sizeof(R) == 8, M, KIND));
         constexpr bool IN_ALONG_MEMBERS = KIND == KIND_STRIDED;
         constexpr bool OUT_ALONG_MEMBERS = KIND != KIND_ROWS;
         // Members are visited in batches of CU whose loads are all issued
@@ -1616,7 +1618,7 @@ constexpr int kCorrThreads = 256;
 
 template <typename R, int M, int KIND>
 __global__ void __launch_bounds__(kCorrThreads) correct_kernel(PassArgs a) {
-    constexpr int C = cfg_C(sizeof(R) == 8, M, KIND);
+    constexpr int C = cfg_CP(sizeof(R) == 8, M, KIND);
     __shared__ cx<double> buf[M];  // the binary64 transform, in place
     __shared__ double scratch[kCorrThreads / 64];
     unsigned long long nrec = a.rep->n_flag;
@@ -1641,7 +1643,7 @@ template <typename R, int M, int KIND, int FT>
 __global__ void __launch_bounds__(cfg_tile_threads(sizeof(R) == 8, M, KIND)) tile_kernel(PassArgs a, TileArgs t) {
     using Cf = PassCfg<R, M, KIND, FT, 0, true>;
     using Shared = PassShared<R, M, KIND, FT, 0, true>;
-    static_assert(Cf::NT % 64 == 0 && (KIND == KIND_ROWS || Cf::CP % Cf::C == 0), "tile kernel shape");
+    static_assert(Cf::NT % 64 == 0 && (KIND == KIND_ROWS || Cf::CN % Cf::C == 0), "tile kernel shape");
     constexpr size_t CORR = FT == FT_BLOCK ? sizeof(cx<double>) * M : 1;  // the correction's binary64 transform
     __shared__ __align__(16) unsigned char pool[sizeof(Shared) > CORR ? sizeof(Shared) : CORR];
     __shared__ double scratch[Cf::NT / 64];

@@ -3,12 +3,15 @@
 // (type, length) in tfft_inst.hip.
 #include <algorithm>
 
+#include "tfft_cols.h"
 #include "tfft_persist.h"
 
 namespace tfft {
 
 TFFT_FOR_EACH_M(TFFT_EXTERN_M, float)
 TFFT_FOR_EACH_M(TFFT_EXTERN_M, double)
+TFFT_FOR_EACH_M(TFFT_EXTERN_COLS, float)
+TFFT_FOR_EACH_M(TFFT_EXTERN_COLS, double)
 TFFT_PERSIST_EXTERN(float, FT_NONE)
 TFFT_PERSIST_EXTERN(float, FT_BLOCK)
 TFFT_PERSIST_EXTERN(double, FT_NONE)
@@ -52,6 +55,11 @@ hipError_t launch_pass(int fp64, int M, int kind, int ft, const PassArgs &a, int
 hipError_t launch_correct(int fp64, int M, int kind, const PassArgs &a, int grid, hipStream_t st) {
     if (fp64) return by_m<double>(M, [&](auto m) { return correct_m<double, decltype(m)::value>(kind, a, grid, st); });
     return by_m<float>(M, [&](auto m) { return correct_m<float, decltype(m)::value>(kind, a, grid, st); });
+}
+
+hipError_t launch_cols(int fp64, int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st) {
+    if (fp64) return by_m<double>(M, [&](auto m) { return cols_m<double, decltype(m)::value>(kind, ft, a, grid, st); });
+    return by_m<float>(M, [&](auto m) { return cols_m<float, decltype(m)::value>(kind, ft, a, grid, st); });
 }
 
 hipError_t launch_tile(int fp64, int M, int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st) {

@@ -111,6 +111,7 @@ struct tfft_plan_s {
     int launched_correct = 0;
     int64_t chunk = 0;           // multi-pass plans: signals per chunk of the batch (= batch: no chunking)
     int persistent = 0;          // shaped for the persistent ragged kernel (tiles of 512 threads)
+    int grid_scale = 0;
     int tile = 0;                // runs as tile launches (use_tiles)
     void *d_tile = nullptr;      // tile launches, one allocation: tickets and states, partial sums
 };
@@ -175,6 +176,8 @@ int shape_pass(tfft_plan_s *p, int idx, int M, int kind, int Guser, int grid_sca
     P.E = cfg_E(fp64, M, kind);
     // the persistent kernel widens every tile to 512 threads (PassCfg with NTHR = 512)
     P.C = p->persistent ? std::max(1, kPersistThreads / (M / P.E)) : cfg_C(fp64, M, kind);
+    if (cfg_CP(fp64, M, kind) == 0 && !p->persistent && p->scheme == TFFT_SCHEME_BLOCK && (Guser == 0 || Guser == 64))
+        P.C = cfg_wide_C(M);
     P.stages = n_stages(M, P.E);
     const int G0 = Guser > 0 ? Guser : (kind == KIND_ROWS ? default_group(M) : 64);
     int64_t tiles;  // workgroup iterations of the pass
@@ -394,6 +397,7 @@ PassArgs pass_args(const tfft_plan_s *p, int i, const ChunkGeom &cg, int64_t nb,
     A.n_strips = P.n_strips;
     A.m1_log2 = ilog2_64(P.m1);
     A.ns_log2 = ilog2_64(P.n_strips);
+    A.c_log2 = ilog2_64(P.C);
     A.o_log2 = ilog2_64(P.O);
     A.n_groups = cg.n_groups;
     A.g_base = cg.g_base;
@@ -454,8 +458,8 @@ int tile_split_log2(const tfft_plan_s *p, const PassPlan &P) {
 // always run as tiles: their pass kernels hold less than a wavefront per
 // workgroup (complex64 N = 16 at 2^24 154 -> 85 / 146 -> 79).  A plan with a
 // grid_scale or a chunk of its own keeps the pass kernels those describe.
-bool use_tiles(const tfft_plan_s *p, int grid_scale) {
-    if (p->persistent || p->scheme != TFFT_SCHEME_BLOCK || grid_scale != 0 || p->chunk < p->batch) return false;
+bool use_tiles(const tfft_plan_s *p) {
+    if (p->persistent || p->scheme != TFFT_SCHEME_BLOCK || p->grid_scale != 0 || p->chunk < p->batch) return false;
     const int fp64 = p->dtype == TFFT_C128;
     bool few = true, small = true;
     for (int i = 0; i < p->passes; ++i) {
@@ -469,6 +473,13 @@ bool use_tiles(const tfft_plan_s *p, int grid_scale) {
         few = few && P.n_groups * ((threads + 63) / 64) <= limit;
     }
     return small || few;
+}
+
+// Whether a pass runs in the column kernel: complex64, whole groups of 64
+// members in its strip width.
+bool use_cols(const tfft_plan_s *p, const PassPlan &P) {
+    return cfg_cols(p->dtype == TFFT_C128, P.M, P.kind) && P.G == 64 && P.C == cfg_wide_C(P.M) && !p->persistent &&
+           std::max(P.n_groups, P.n_outer) < (int64_t(1) << 30);
 }
 
 // Device buffers of one execution: the report counters, the records and the
@@ -532,6 +543,11 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
                 TileArgs T = P.tile;
                 T.fix = mode == TFFT_FT_CORRECT;
                 if (launch_tile(fp64, P.M, P.kind, scheme_ft, A, T, st) != hipSuccess) return TFFT_E_HIP;
+            } else if (use_cols(p, P) && scheme_ft <= FT_BLOCK) {
+                const int64_t most = p->grid_scale >= 0 ? (int64_t)TFFT_COL_GRID << p->grid_scale
+                                                        : (int64_t)TFFT_COL_GRID >> -p->grid_scale;
+                const int grid = (int)std::min<int64_t>((cg.n_groups + 7) / 8 * 8, most * (P.M == 64 ? 2 : 1));
+                if (launch_cols(fp64, P.M, P.kind, scheme_ft, A, grid, st) != hipSuccess) return TFFT_E_HIP;
             } else if (launch_pass(fp64, P.M, P.kind, scheme_ft, A, cg.grid, st) != hipSuccess) {
                 return TFFT_E_HIP;
             }
@@ -623,6 +639,7 @@ int shape_plan(tfft_plan_s *p, int64_t n, int64_t batch, int dtype, const tfft_o
     p->flags = flags;
     p->kappa = (opt && opt->kappa > 0) ? opt->kappa : (dtype == TFFT_C128 ? TFFT_KAPPA64 : TFFT_KAPPA32);
     p->scheme = scheme;
+    p->grid_scale = grid_scale;
     p->persistent = (flags & TFFT_PERSISTENT) ? 1 : 0;
     // one pass up to 2^13 (the paper's single-launch limit); two passes up to
     // 2^19 (complex64) / 2^20; three passes above, the shortest first (tiles
@@ -757,7 +774,7 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
         else if (hipMemset(p->d_rep, 0, sizeof(DevReport)) != hipSuccess)
             rc = TFFT_E_HIP;
     }
-    p->tile = use_tiles(p, opt ? opt->grid_scale : 0);
+    p->tile = use_tiles(p);
     if (rc == TFFT_OK && p->tile) rc = tile_buffers(p);
     if (rc == TFFT_OK && host_off) {
         std::vector<int64_t> off(host_off, host_off + batch);
@@ -809,7 +826,13 @@ tfft_record host_record(const tfft_plan_s *p, const DevRecord &d) {
     const PassPlan &P = p->pass[pass_ok ? d.pass : 0];
     // a member outside the group (never written by the kernels) reads as
     // the group's first signal
-    const int mem = (d.member >= 0 && d.member < P.G) ? d.member : 0;
+    int member = d.member, method = d.method;
+    if (member == kUnlocated) {  // DETECT mode: no correction has looked at it
+        const int64_t left = P.n_outer - d.group / P.n_strips * P.rb;
+        member = quotient_member(d.d1r, d.d1i, d.d2r, d.d2i, P.C * (int)std::min<int64_t>(left, P.rb));
+        method = member >= 0 ? TFFT_LOC_QUOTIENT : TFFT_LOC_NONE;
+    }
+    const int mem = (member >= 0 && member < P.G) ? member : 0;
     if (P.kind == KIND_ROWS) {
         r.signal = d.group * P.G + mem;
         r.sub = d.method == TFFT_LOC_THREAD ? (int64_t)d.s : 0;
@@ -827,9 +850,9 @@ tfft_record host_record(const tfft_plan_s *p, const DevRecord &d) {
     if (r.signal < 0 || r.signal >= p->batch) r.signal = std::min<int64_t>(p->batch - 1, std::max<int64_t>(0, r.signal));
     r.group = d.group;
     r.pass = d.pass;
-    r.member = d.member;
+    r.member = member;
     r.action = d.action;
-    r.method = d.method;
+    r.method = method;
     r.residual = std::sqrt(d.d1r * d.d1r + d.d1i * d.d1i);
     r.threshold = d.tau;
     const double den = d.d1r * d.d1r + d.d1i * d.d1i;
