@@ -261,6 +261,11 @@ constexpr bool cfg_defer(int fp64, int M, int kind) {
 constexpr int cfg_pf_fence(int fp64, int M, int kind) {
     return TFFT_PF_FENCE && (kind != KIND_ROWS || M >= TFFT_PF_FENCE_ROWS_MIN) ? 1 : 0;
 }
+// Rows whose groups of 64 signals (fewer from 2048 points on) take 256 KiB or
+// more: their pass kernels may share a group between workgroups and begin each
+// at a signal of its own.  Shorter ones gain from neither and lost 2% to the
+// scalar registers it takes.
+constexpr bool cfg_turns(int fp64, int M, int kind) { return kind == KIND_ROWS && M >= (fp64 ? 256 : 512) && M <= 4096; }
 constexpr int cfg_threads(int fp64, int M, int kind) { return cfg_C(fp64, M, kind) * (M / cfg_E(fp64, M, kind)); }
 // Prefetch of the next tile straight into a second LDS buffer
 // (global_load_lds_dwordx4: 16-byte elements, i.e. complex128) for tiles of
@@ -409,6 +414,11 @@ struct PassArgs {
     int32_t ns_log2;    // multi-pass: log2(n_strips)
     int32_t o_log2;     // STRIDED: log2(O)
     int32_t c_log2;     // multi-pass: log2 of the sub-signals per strip
+    int32_t split_log2; // a group's rounds are shared by 2^split_log2 turns of the workgroups:
+    double *part;       // [n_groups << split_log2][5] their sums
+    uint32_t *tick;     // [n_groups * kTickStride] turns done, 0 between launches
+    int32_t rot_mul;    // rows: turn w begins at round (w >> rot_shift) * rot_mul of its rounds, and wraps
+    int32_t rot_shift;
 };
 
 // What a tile launch needs besides PassArgs: a group's tiles are split over

@@ -695,7 +695,7 @@ struct PassHooks {
 // TILE: only the rounds r_first..r_end - 1 of the one group g_first; its part
 // of the five group sums goes to tile_sums (LDS) and nothing is decided.
 // tile_through: the outputs are stored through the caches.
-template <typename R, int M, int KIND, int FT, int NTHR, bool TILE = false>
+template <typename R, int M, int KIND, int FT, int NTHR, bool TILE = false, bool TURNS = false>
 __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KIND, FT, NTHR, TILE> &sh, cx<R> *nbuf,
                                           int64_t g_first, int64_t g_end, int64_t g_step, const PassHooks &hk,
                                           int r_first = 0, int r_end = 0, double *tile_sums = nullptr,
@@ -813,9 +813,19 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
     const double rotr = jr == 0 ? 1.0 : kW3r;
     const double roti = jr == 0 ? 0.0 : (jr == 1 ? kW3i : -kW3i);
 
+    // TURNS (one-pass plans): a turn w is a group, or its share of the rounds where
+    // 2^split_log2 workgroups share the group; it begins at a round of its own
+    // (rot_mul) and wraps, so that neighbouring workgroups do not walk the
+    // memory channels in step (complex64, 1 GiB, N = 4096: 4.1 -> 4.8 TB/s).
     // FT_SIGNAL: a tile of C signals per iteration, each its own group (G = 1)
-    const int rounds = SIGR ? 1 : (TILE ? r_end : a.G / C);
-    const int64_t n_iter = g_end;
+    const int sp = TURNS ? a.split_log2 : 0;
+    const int rounds = SIGR ? 1 : (TILE ? r_end - r_first : (a.G / C) >> sp);
+    const int64_t n_iter = TURNS ? a.n_groups : g_end;
+    auto round_of = [&](int64_t w, int i) -> int {
+        if constexpr (TILE) return r_first + i;
+        else if constexpr (!TURNS) return i;
+        else return (int)(w & ((1 << sp) - 1)) * rounds + ((((int)w >> a.rot_shift) * a.rot_mul + i) & (rounds - 1));
+    };
     auto mloc = [&](int64_t gg, int rr) -> MemberLoc {
         if constexpr (SIGR) return member_loc<M, KIND, CP>(a, gg * C + c, 0);
         else return member_loc<M, KIND, CP>(a, gg, rr * C + c);
@@ -878,8 +888,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
             }
         }
     };
-    if constexpr (PREFETCH) load_tile(g_first, 0);
-    if constexpr (LDSPF) dma_tile(g_first, 0);
+    if constexpr (PREFETCH) load_tile(g_first >> sp, round_of(g_first, 0));
+    if constexpr (LDSPF) dma_tile(g_first >> sp, round_of(g_first, 0));
     // Deferred stores (LDS-prefetching row tiles): a tile's outputs stay in
     // registers and are stored right after the next tile's prefetch has been
     // waited for, so that the wait (which also counts stores) never waits
@@ -971,8 +981,21 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
         }
         if constexpr (NT > 64) tile_sync();
     };
-    // a group's decision from its five sums (one thread)
-    auto decide = [&](const double *t, int64_t g) {
+    // a group's decision from the five sums of turn w (one thread): where turns
+    // share the group, by the last of them, from all sums in their order
+    auto decide = [&](double *t, int64_t w) {
+        const int64_t g = w >> sp;
+        if (sp > 0) {
+            double *part = a.part + (g << sp) * 5;
+#pragma unroll
+            for (int q = 0; q < 5; ++q) agent_store(part + (w & ((1 << sp) - 1)) * 5 + q, t[q]);
+            vm_wait_all();  // the sums before the ticket
+            if (atomicInc(a.tick + g * kTickStride, (1u << sp) - 1) != (1u << sp) - 1) return;
+#pragma unroll
+            for (int q = 0; q < 5; ++q) t[q] = 0.0;
+            for (int i = 0; i < 1 << sp; ++i)
+                for (int q = 0; q < 5; ++q) t[q] += agent_load(part + i * 5 + q);
+        }
         DevRecord rc;
         if (decide_group<KIND, CP>(a, t, g, rc)) {
             const unsigned long long slot = atomicAdd(&a.rep->n_flag, 1ULL);
@@ -980,9 +1003,10 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
             if ((int64_t)slot < a.rec_cap) a.recs[slot] = rc;
         }
     };
-    int64_t g_prev = -1;  // RED_DEFER: the group whose decision is pending
-    int it = 0;           // RED_DEFER: groups done by this workgroup
-    for (int64_t g = g_first; g < n_iter; g += g_step) {
+    int64_t w_prev = -1;  // RED_DEFER: the turn whose decision is pending
+    int it = 0;           // RED_DEFER: turns done by this workgroup
+    for (int64_t w = g_first; w < g_end; w += g_step) {
+        const int64_t g = w >> sp;
         const int64_t gsig = g * C + c;  // FT_SIGNAL: this thread's signal (= its group)
         // the fault lookup reads a table entry or a constant -1 (no branch)
         const int32_t *fhp;
@@ -1003,7 +1027,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
         }
         double D1r = 0.0, D1i = 0.0, D2r = 0.0, D2i = 0.0;
         double Ssum = 0.0;  // energy of the group's inputs (binary64), for the threshold only
-        for (int r = TILE ? r_first : 0; r < rounds; ++r) {
+        for (int i = 0; i < rounds; ++i) {
+            const int r = round_of(w, i);
             const int b = SIGR ? 0 : r * C + c;
             // TILE: opaque per round, so that tables and LDS addresses are
             // formed again for every tile instead of held in registers
@@ -1052,8 +1077,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
                     asm volatile("" ::: "memory");
                 }
                 flush();
-                if (r + 1 < rounds) load_tile(g, r + 1);
-                else load_tile(g + g_step, 0);
+                if (i + 1 < rounds) load_tile(g, round_of(w, i + 1));
+                else load_tile((w + g_step) >> sp, round_of(w + g_step, 0));
             } else {
                 load_tile(g, r);
 #pragma unroll
@@ -1102,8 +1127,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
                 // drained by now): an older store still counted would make
                 // the first exchange after the DMA wait for the whole queue.
                 vm_wait_all();
-                if (r + 1 < rounds) dma_tile(g, r + 1);
-                else dma_tile(g + g_step, 0);
+                if (i + 1 < rounds) dma_tile(g, round_of(w, i + 1));
+                else dma_tile((w + g_step) >> sp, round_of(w + g_step, 0));
             }
             if (a.conj_in) {
 #pragma unroll
@@ -1316,7 +1341,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
                         for (int w = tid; w < NT; w += 64) v[q] += part[q * NT + w];
                         v[q] = wave_sum_dpp(v[q], Dpp64{});
                     }
-                    if (tid == 63) decide(v, g);
+                    if (tid == 63) decide(v, w);
                 }
                 tile_sync();
             } else {
@@ -1345,21 +1370,21 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
                     // the previous group's sums were written before this
                     // group's exchange barriers; this group's go to the other
                     // slot, which is read only after the next group's barriers
-                    if (tid == 0 && g_prev >= 0) {
+                    if (tid == 0 && w_prev >= 0) {
                         double t[5] = {0, 0, 0, 0, 0};
-                        for (int w = 0; w < WAVES; ++w)
-                            for (int k = 0; k < 5; ++k) t[k] += redg[(it - 1) & 1][w][k];
-                        decide(t, g_prev);
+                        for (int v = 0; v < WAVES; ++v)
+                            for (int k = 0; k < 5; ++k) t[k] += redg[(it - 1) & 1][v][k];
+                        decide(t, w_prev);
                     }
-                    g_prev = g;
+                    w_prev = w;
                     ++it;
                 } else {
                     tile_sync();
                     if (tid == 0) {
                         double t[5] = {0, 0, 0, 0, 0};
-                        for (int w = 0; w < WAVES; ++w)
-                            for (int k = 0; k < 5; ++k) t[k] += red[w][k];
-                        decide(t, g);
+                        for (int v = 0; v < WAVES; ++v)
+                            for (int k = 0; k < 5; ++k) t[k] += red[v][k];
+                        decide(t, w);
                     }
                     tile_sync();
                 }
@@ -1369,19 +1394,18 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
     if constexpr (RED_DEFER) {
         // the last group's decision
         tile_sync();
-        if (tid == 0 && g_prev >= 0) {
+        if (tid == 0 && w_prev >= 0) {
             double t[5] = {0, 0, 0, 0, 0};
-            for (int w = 0; w < WAVES; ++w)
-                for (int k = 0; k < 5; ++k) t[k] += redg[(it - 1) & 1][w][k];
-            decide(t, g_prev);
+            for (int v = 0; v < WAVES; ++v)
+                for (int k = 0; k < 5; ++k) t[k] += redg[(it - 1) & 1][v][k];
+            decide(t, w_prev);
         }
     }
     flush();
 }
 
-template <typename R, int M, int KIND, int FT>
-__global__ void __launch_bounds__(cfg_threads(sizeof(R) == 8, M, KIND)) TFFT_PASS_OCCUPANCY
-pass_kernel(PassArgs a) {
+template <typename R, int M, int KIND, int FT, bool TURNS>
+__device__ __forceinline__ void run_pass(const PassArgs &a) {
     using Cf = PassCfg<R, M, KIND, FT>;
     __shared__ PassShared<R, M, KIND, FT> sh;
     __shared__ __align__(16) cx<R> nbuf[pass_nbuf_elems<R, M, KIND, FT>()];
@@ -1390,8 +1414,25 @@ pass_kernel(PassArgs a) {
     const int nwg = gridDim.x;
     int64_t wl = blockIdx.x;
     if (nwg % 8 == 0) wl = (blockIdx.x % 8) * (nwg / 8) + blockIdx.x / 8;
-    const int64_t n_iter = Cf::SIGR ? (a.n_groups + Cf::C - 1) / Cf::C : a.n_groups;
-    pass_body<R, M, KIND, FT, 0>(a, sh, nbuf, wl, n_iter, nwg, PassHooks{nullptr, nullptr, 0});
+    const int64_t turns = Cf::SIGR ? (a.n_groups + Cf::C - 1) / Cf::C
+                                   : (TURNS ? a.n_groups << a.split_log2 : a.n_groups);
+    pass_body<R, M, KIND, FT, 0, false, TURNS>(a, sh, nbuf, wl, turns, nwg, PassHooks{nullptr, nullptr, 0});
+}
+
+template <typename R, int M, int KIND, int FT>
+__global__ void __launch_bounds__(cfg_threads(sizeof(R) == 8, M, KIND)) TFFT_PASS_OCCUPANCY
+pass_kernel(PassArgs a) {
+    run_pass<R, M, KIND, FT, false>(a);
+}
+
+// The rows' pass kernel with turns (pass_body): groups shared between
+// workgroups, or begun at a signal of the workgroup's own.  A kernel of its own
+// because it takes more scalar registers than there are: short groups, which gain
+// nothing, lost 1-2% to them.
+template <typename R, int M, int FT>
+__global__ void __launch_bounds__(cfg_threads(sizeof(R) == 8, M, KIND_ROWS)) TFFT_PASS_OCCUPANCY
+turn_kernel(PassArgs a) {
+    run_pass<R, M, KIND_ROWS, FT, true>(a);
 }
 
 // ------------------------------------------------------- correction kernel
@@ -1730,6 +1771,12 @@ hipError_t tile_m(int kind, int ft, const PassArgs &a, const TileArgs &t, hipStr
 template <typename R, int M, int KIND, int FT>
 static hipError_t launch_one(const PassArgs &a, int grid, hipStream_t st) {
     constexpr int NT = cfg_threads(sizeof(R) == 8, M, KIND);
+    if constexpr (cfg_turns(sizeof(R) == 8, M, KIND) && (FT == FT_NONE || FT == FT_BLOCK)) {
+        if (a.split_log2 > 0 || a.rot_mul > 0) {
+            hipLaunchKernelGGL((turn_kernel<R, M, FT>), dim3(grid), dim3(NT), 0, st, a);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((pass_kernel<R, M, KIND, FT>), dim3(grid), dim3(NT), 0, st, a);
     return hipGetLastError();
 }

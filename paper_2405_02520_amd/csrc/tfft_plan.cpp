@@ -64,6 +64,7 @@ cd unit_root(int64_t t, int64_t n) {
 struct PassPlan {
     int M = 0, kind = 0, E = 0, C = 0, G = 0, rb = 1, stages = 0;
     int64_t n_strips = 1, n_groups = 0, n_outer = 0;
+    int split_log2 = 0;  // pass kernels: a group's rounds are shared by 2^split_log2 workgroups
     int64_t L = 0, rows = 0, tw_scale = 1;
     int S = 1, O = 1, m1 = 1, m2 = 1;
     int grid = 0;
@@ -261,10 +262,10 @@ int upload_pass(tfft_plan_s *p, int idx) {
         if ((rc = upload((float **)&P.d_stw, w32)) != TFFT_OK) return rc;
     }
     if ((rc = upload(&P.d_stw64, w64)) != TFFT_OK) return rc;
-    const bool last = idx == p->passes - 1;
     if ((rc = upload(&P.d_cfwd, checksum_vec(M, false, 1.0))) != TFFT_OK) return rc;
     if ((rc = upload(&P.d_cinv_unscaled, checksum_vec(M, true, 1.0))) != TFFT_OK) return rc;
-    if ((rc = upload(&P.d_cinv, checksum_vec(M, true, last ? 1.0 / (double)p->n : 1.0))) != TFFT_OK) return rc;
+    if ((rc = upload(&P.d_cinv, checksum_vec(M, true, idx == p->passes - 1 ? 1.0 / (double)p->n : 1.0))) != TFFT_OK)
+        return rc;
     return TFFT_OK;
 }
 
@@ -348,7 +349,7 @@ ChunkGeom chunk_geom(const tfft_plan_s *p, const PassPlan &P, int64_t c0, int64_
         c.g_base = P.n_strips * (c0 * per / P.rb);
         tiles = c.n_groups;
     }
-    int64_t grid = std::min<int64_t>(tiles, P.grid);
+    int64_t grid = P.split_log2 > 0 ? tiles << P.split_log2 : std::min<int64_t>(tiles, P.grid);
     if (grid >= 8) grid = (grid + 7) / 8 * 8;
     c.grid = (int)std::max<int64_t>(1, grid);
     return c;
@@ -398,6 +399,25 @@ PassArgs pass_args(const tfft_plan_s *p, int i, const ChunkGeom &cg, int64_t nb,
     A.m1_log2 = ilog2_64(P.m1);
     A.ns_log2 = ilog2_64(P.n_strips);
     A.c_log2 = ilog2_64(P.C);
+    A.split_log2 = P.split_log2;
+    A.part = P.tile.part;
+    A.tick = P.tile.tick;
+    if (P.kind == KIND_ROWS) {
+        // Workgroups that all begin at the first signal of their groups stay a
+        // power of two of bytes apart for the whole pass and crowd the same
+        // memory channels: neighbours begin a quarter of a group apart, and
+        // groups of more than 512 KiB a tile apart in pairs.  Measured (us,
+        // 1 GiB, begun at the first signal - quarters - a tile apart in pairs):
+        // complex64 (512 KiB) N = 1024 275 - 207 - 212, N = 4096 285 - 215 -
+        // 221; complex128 N = 512 (512 KiB) 459 - 414 - 425, N = 1024 (1 MiB)
+        // 418 - 436 - 423 and at 512 MiB 257 - 222 - 216.  Groups below 256 KiB
+        // gain nothing (complex64 N = 1024 in groups of 16: 116, quarters 119), nor
+        // do tiles of 64 KiB (complex128 N = 4096 509, a tile apart in pairs 517).
+        const int rounds = std::max(1, P.G / P.C) >> P.split_log2;
+        const int64_t bytes = (int64_t)P.G * P.M * (fp64 ? 16 : 8);
+        A.rot_mul = bytes < (256 << 10) || P.M * (fp64 ? 16 : 8) >= 65536 ? 0 : (bytes > (512 << 10) ? 1 : std::max(1, rounds / 4));
+        A.rot_shift = bytes > (512 << 10) ? 1 : 0;
+    }
     A.o_log2 = ilog2_64(P.O);
     A.n_groups = cg.n_groups;
     A.g_base = cg.g_base;
@@ -446,18 +466,20 @@ int tile_split_log2(const tfft_plan_s *p, const PassPlan &P) {
 // tiles, spread over the chip, take over where every pass's launch would hold
 // few wavefronts.  Measured (us per call, pass kernels then tiles; FT CORRECT /
 // OFF): complex64 N = 256 at 2^14 elements (4 wavefronts) 18 -> 6 / 15 -> 3.5;
-// N = 1024 at 2^20 (64) 78 -> 11 / 70 -> 8, at 2^23 (512) 86 -> 45 / 78 -> 35,
-// at 2^24 (1024) 93 -> 98 / 87 -> 81; N = 2^14 at 2^20 (1024) 27 -> 19 / 19 ->
-// 13; N = 2^16 at 2^21 (1024) 40 -> 33 / 30 -> 20, at 2^22 (2048) 44 -> 56 /
-// 35 -> 33; complex128 N = 4096 at 2^23 (1024) 126 -> 87 / 158 -> 66: the line
-// lies at 1024 wavefronts.  It lies lower where the tile kernel holds one
-// 512-thread workgroup per CU but the pass kernel streams well: complex64 rows
-// of 4096 points (at 512 wavefronts 52 -> 39 / 47 -> 24, at 1024 55 -> 67 /
-// 49 -> 43) and strided passes of 1024 (complex128 N = 2^20 at 128 wavefronts
-// 44 -> 36 / 38 -> 32, at 512 83 -> 106 / 80 -> 73).  Signals of up to 16 points
-// always run as tiles: their pass kernels hold less than a wavefront per
-// workgroup (complex64 N = 16 at 2^24 154 -> 85 / 146 -> 79).  A plan with a
-// grid_scale or a chunk of its own keeps the pass kernels those describe.
+// N = 1024 at 2^20 (64) 78 -> 11 / 70 -> 8; N = 2^14 at 2^20 (1024) 27 -> 19 /
+// 19 -> 13; N = 2^16 at 2^21 (1024) 40 -> 33 / 30 -> 20, at 2^22 (2048) 44 -> 56
+// / 35 -> 33: the line lies at 1024 wavefronts.  It lies lower for rows of 1024
+// points and more, whose pass kernel shares a group between workgroups as well
+// (pass_split_log2) but holds the tables in registers: complex64 N = 1024 at
+// 2^23 (512) 39 -> 44 / 34 -> 34, at 2^22 (256) 25 -> 26 / 20 -> 18; N = 4096 at
+// 2^22 (512) 26 -> 31 / 21 -> 24, at 2^21 (256) 20 -> 16 / 15 -> 14; complex128
+// N = 1024 at 2^24 (1024) 115 -> 133 / 116 -> 123, at 9968 signals (624) 94 ->
+// 85, at 2^23 (512) 67 -> 69 / 64 -> 60, N = 4096 at 2^23 (1024) 77 -> 87 / 87 -> 67; and for strided passes of 1024
+// (complex128 N = 2^20 at 128 wavefronts 44 -> 36 / 38 -> 32, at 512 83 -> 106 /
+// 80 -> 73).  Signals of up to 16 points always run as tiles: their pass kernels
+// hold less than a wavefront per workgroup (complex64 N = 16 at 2^24 154 -> 85 /
+// 146 -> 79).  A plan with a grid_scale or a chunk of its own keeps the pass
+// kernels those describe.
 bool use_tiles(const tfft_plan_s *p) {
     if (p->persistent || p->scheme != TFFT_SCHEME_BLOCK || p->grid_scale != 0 || p->chunk < p->batch) return false;
     const int fp64 = p->dtype == TFFT_C128;
@@ -467,7 +489,7 @@ bool use_tiles(const tfft_plan_s *p) {
         if (tile_rounds(p, P) < 1) return false;
         const int threads = cfg_threads(fp64, P.M, P.kind);
         int64_t limit = TFFT_TILE_MAX_WAVES;
-        if (P.kind == KIND_ROWS && P.M >= 4096 && !fp64) limit /= 2;
+        if (P.kind == KIND_ROWS && P.M >= 1024) limit = limit * (fp64 ? (P.M >= 4096 ? 4 : 3) : 1) / 4;
         if (P.kind == KIND_STRIDED && P.M >= 1024) limit /= 4;
         small = small && threads < 64;
         few = few && P.n_groups * ((threads + 63) / 64) <= limit;
@@ -480,6 +502,26 @@ bool use_tiles(const tfft_plan_s *p) {
 bool use_cols(const tfft_plan_s *p, const PassPlan &P) {
     return cfg_cols(p->dtype == TFFT_C128, P.M, P.kind) && P.G == 64 && P.C == cfg_wide_C(P.M) && !p->persistent &&
            std::max(P.n_groups, P.n_outer) < (int64_t(1) << 30);
+}
+
+// log2 of the workgroups that share a group of a one-pass plan's pass kernel:
+// enough of them to fill the chip, where the groups alone do not (complex64
+// N = 4096 at 2^23 elements, 128 groups on 256 CUs: 54 us, halves 38; N = 1024
+// at 2^24, 256 groups where 512 workgroups are resident: 92, halves 61;
+// complex128 N = 4096 at 2^23: 126, quarters 77), and no more (N = 4096 at 2^24,
+// 256 groups: whole 62, halves 69).  The multi-pass kinds keep whole groups: the
+// shared form cost their kernels 1-4% unused (more scalar registers than there
+// are), and used it lost 5-40% (their tiles' rows lie in other tiles' lines).
+int pass_split_log2(const tfft_plan_s *p, const PassPlan &P) {
+    if (p->persistent || p->scheme != TFFT_SCHEME_BLOCK || p->grid_scale != 0 ||
+        !cfg_turns(p->dtype == TFFT_C128, P.M, P.kind))
+        return 0;
+    int cus = 0;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
+    const int64_t resident = (int64_t)cus * std::max(1, pass_occupancy(p->dtype == TFFT_C128, P.M, P.kind, FT_BLOCK));
+    int k = 0;
+    while ((P.n_groups << k) < resident && (P.G / P.C) >> (k + 1) >= 1) ++k;
+    return k;
 }
 
 // Device buffers of one execution: the report counters, the records and the
@@ -693,15 +735,15 @@ int shape_plan(tfft_plan_s *p, int64_t n, int64_t batch, int dtype, const tfft_o
     return TFFT_OK;
 }
 
-// The tile launches' memory: the tickets (shared by the passes, which run one
+// The memory of tile launches and of shared groups: the tickets (shared by the passes, which run one
 // after the other, and zero between launches), every pass's group states, the
 // partial sums (shared as well).
 int tile_buffers(tfft_plan_s *p) {
     int64_t parts = 0, groups = 0, all = 0;
     for (int i = 0; i < p->passes; ++i) {
         PassPlan &P = p->pass[i];
-        P.tile.split_log2 = tile_split_log2(p, P);
-        P.tile.rounds = tile_rounds(p, P) >> P.tile.split_log2;
+        P.tile.split_log2 = p->tile ? tile_split_log2(p, P) : P.split_log2;
+        P.tile.rounds = p->tile ? tile_rounds(p, P) >> P.tile.split_log2 : 0;
         P.tile.rec0 = all;
         parts = std::max(parts, P.n_groups << P.tile.split_log2);
         if (P.tile.split_log2 > 0) groups = std::max(groups, P.n_groups);
@@ -775,7 +817,13 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
             rc = TFFT_E_HIP;
     }
     p->tile = use_tiles(p);
-    if (rc == TFFT_OK && p->tile) rc = tile_buffers(p);
+    bool split = false;
+    for (int i = 0; i < p->passes && !p->tile; ++i) {
+        PassPlan &P = p->pass[i];
+        P.split_log2 = pass_split_log2(p, P);
+        split = split || P.split_log2 > 0;
+    }
+    if (rc == TFFT_OK && (p->tile || split)) rc = tile_buffers(p);
     if (rc == TFFT_OK && host_off) {
         std::vector<int64_t> off(host_off, host_off + batch);
         rc = upload(&p->d_sig_off, off);
