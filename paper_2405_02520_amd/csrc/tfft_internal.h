@@ -419,6 +419,8 @@ struct PassArgs {
     uint32_t *tick;     // [n_groups * kTickStride] turns done, 0 between launches
     int32_t rot_mul;    // rows: turn w begins at round (w >> rot_shift) * rot_mul of its rounds, and wraps
     int32_t rot_shift;
+    const double *ckappa; // complex128 tile kernels, [M]: c_n = cf (1 + i ckappa_n)
+    double cf_re, cf_im;
 };
 
 // What a tile launch needs besides PassArgs: a group's tiles are split over

@@ -73,6 +73,7 @@ struct PassPlan {
     double *d_cfwd = nullptr;    // checksum vector, forward
     double *d_cinv = nullptr;    // checksum vector, inverse (scaled for the last pass)
     double *d_cinv_unscaled = nullptr;
+    double *d_kappa = nullptr;   // tile kernels: checksum_kappa, forward then inverse
     int32_t *d_fault_head = nullptr;
     DevFault *d_faults = nullptr;
     double tau_coef = 0.0;
@@ -151,7 +152,23 @@ int default_group(int M) {
 // q = (M +- 3n) mod 3M, so the sum is geometric: (1 - w_3^M) / (1 - w_{3M}^q).
 // Writing w_{3M}^q = v^2 with v = w_{6M}^q, 1 - v^2 = v (conj(v) - v) =
 // -2i Im(v) v, which has no cancellation; v comes from the exactly reduced
-// root, so each entry is within a few ulp.
+// root, so each entry is within a few ulp.  conj(v) / (-2i Im v) is 1/2 + i Re v
+// / (2 Im v): c_n = f (1 + i kappa_n) with f = s (1 - w_3^M) / 2 and kappa_n =
+// Re v / Im v, which is what the tile kernels read.
+cd checksum_factor(int M) { return 0.5 * (1.0 - unit_root(M % 3, 3)); }
+
+std::vector<double> checksum_kappa(int M, bool inverse) {
+    std::vector<double> out((size_t)M);
+    const int64_t M3 = 3 * (int64_t)M;
+    for (int n = 0; n < M; ++n) {
+        int64_t q = ((int64_t)M + (inverse ? -3 : 3) * (int64_t)n) % M3;
+        if (q < 0) q += M3;
+        const cd v = unit_root(q, 2 * M3);
+        out[(size_t)n] = v.real() / v.imag();
+    }
+    return out;
+}
+
 std::vector<double> checksum_vec(int M, bool inverse, double scale) {
     std::vector<double> out(2 * (size_t)M);
     const cd num = 1.0 - unit_root(M % 3, 3);
@@ -266,7 +283,10 @@ int upload_pass(tfft_plan_s *p, int idx) {
     if ((rc = upload(&P.d_cinv_unscaled, checksum_vec(M, true, 1.0))) != TFFT_OK) return rc;
     if ((rc = upload(&P.d_cinv, checksum_vec(M, true, idx == p->passes - 1 ? 1.0 / (double)p->n : 1.0))) != TFFT_OK)
         return rc;
-    return TFFT_OK;
+    std::vector<double> kappa = checksum_kappa(M, false);
+    const std::vector<double> inv = checksum_kappa(M, true);
+    kappa.insert(kappa.end(), inv.begin(), inv.end());
+    return upload(&P.d_kappa, kappa);
 }
 
 void free_plan(tfft_plan_s *p) {
@@ -280,6 +300,7 @@ void free_plan(tfft_plan_s *p) {
         (void)hipFree(P.d_cfwd);
         (void)hipFree(P.d_cinv);
         (void)hipFree(P.d_cinv_unscaled);
+        (void)hipFree(P.d_kappa);
         (void)hipFree(P.d_fault_head);
         (void)hipFree(P.d_faults);
     }
@@ -425,6 +446,10 @@ PassArgs pass_args(const tfft_plan_s *p, int i, const ChunkGeom &cg, int64_t nb,
     A.conj_out = inverse ? 1 : 0;
     A.out_scale = (inverse && last && !(p->flags & TFFT_INVERSE_UNSCALED)) ? 1.0 / (double)p->n : 1.0;
     A.cvec = !inverse ? P.d_cfwd : ((p->flags & TFFT_INVERSE_UNSCALED) ? P.d_cinv_unscaled : P.d_cinv);
+    A.ckappa = P.d_kappa + (inverse ? P.M : 0);
+    const cd cf = checksum_factor(P.M) * A.out_scale;
+    A.cf_re = cf.real();
+    A.cf_im = cf.imag();
     A.stw = P.d_stw;
     A.stw64 = P.d_stw64;
     A.itw_lo = p->d_itw_lo;
