@@ -719,12 +719,12 @@ struct PassHooks {
 // by one workgroup of PassCfg::NT threads with the LDS of `sh`.
 // TILE: only the rounds r_first..r_end - 1 of the one group g_first; its part
 // of the five group sums goes to tile_sums (LDS) and nothing is decided.
-// tile_through: the outputs are stored through the caches.
+// through (TILE; NTHR strided passes): the outputs are stored through the caches.
 template <typename R, int M, int KIND, int FT, int NTHR, bool TILE = false, bool TURNS = false>
 __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KIND, FT, NTHR, TILE> &sh, cx<R> *nbuf,
                                           int64_t g_first, int64_t g_end, int64_t g_step, const PassHooks &hk,
                                           int r_first = 0, int r_end = 0, double *tile_sums = nullptr,
-                                          bool tile_through = false) {
+                                          bool through = false) {
     using Cf = PassCfg<R, M, KIND, FT, NTHR, TILE>;
     constexpr int FP64 = Cf::FP64;
     constexpr bool BLK = Cf::BLK, SIG = Cf::SIG, THR = Cf::THR;
@@ -770,8 +770,8 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
     const cx<R> *in = reinterpret_cast<const cx<R> *>(a.in);
     cx<R> *out = reinterpret_cast<cx<R> *>(a.out);
     auto store = [&](cx<R> *p, cx<R> v) {
-        if constexpr (TILE && BLK) {
-            if (tile_through) {
+        if constexpr ((TILE && BLK) || (NTHR > 0 && KIND == KIND_STRIDED)) {
+            if (through) {
                 agent_store(p, v);
                 return;
             }
@@ -929,7 +929,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, PassShared<R, M, KI
         if constexpr (DEFER) {
             if (pend) {
 #pragma unroll
-                for (int m = 0; m < E; ++m) st_stream<R, NT_ST>(pdst + (uint32_t)(T * m) * pstr, ps[m]);
+                for (int m = 0; m < E; ++m) store(pdst + (uint32_t)(T * m) * pstr, ps[m]);
             }
             pend = false;
         }

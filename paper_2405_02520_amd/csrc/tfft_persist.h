@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(kPThreads) persist_kernel(PQueue q, const PIte
 #define TFFT_PV_RUN(K, MM)                                                                                     \
     case pvariant_id(K, MM):                                                                                   \
         pass_body<R, MM, K, FT, kPThreads>(a, *reinterpret_cast<PassShared<R, MM, K, FT, kPThreads> *>(pool), \
-                                           reinterpret_cast<cx<R> *>(npool), item.g0, item.g1, item.step, hk); \
+                                           reinterpret_cast<cx<R> *>(npool), item.g0, item.g1, item.step, hk, 0, 0, nullptr, publish != 0); \
         break;
             TFFT_PVARIANTS(TFFT_PV_RUN)
 #undef TFFT_PV_RUN
@@ -159,10 +159,12 @@ __global__ void __launch_bounds__(kPThreads) persist_kernel(PQueue q, const PIte
                 break;
         }
         __syncthreads();
+        bool fixed = false;
         if constexpr (FT == FT_BLOCK) {
             // the flagged groups of this item, corrected before it is released
             const int ns = __builtin_amdgcn_readfirstlane(n_slots);
             if (fix && ns > 0) {
+                fixed = true;
                 for (int k = 0; k < ns; ++k) {
                     const int64_t slot = uniform64(slots[k]);
                     if (slot >= a.rec_cap) continue;  // dropped record: reported as such
@@ -180,9 +182,13 @@ __global__ void __launch_bounds__(kPThreads) persist_kernel(PQueue q, const PIte
                 }
             }
         }
-        // release (when a later pass reads this output): every wavefront's
-        // stores visible at agent scope, then the count
-        if (publish) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        // release (when a later pass reads this output): the outputs went
+        // through the caches, so once every wavefront's stores are done they are
+        // visible at agent scope, then the count.  (A release fence instead
+        // writes the chiplet's whole L2 back, once per wavefront and item.)
+        // Corrected outputs were stored through the caches' usual way: a fence.
+        if (publish && fixed) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (publish) vm_wait_all();
         __syncthreads();
         if (wave == 0 && publish)
             __hip_atomic_fetch_add(q.done + done_at, (int32_t)one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
