@@ -194,8 +194,6 @@ int shape_pass(tfft_plan_s *p, int idx, int M, int kind, int Guser, int grid_sca
     P.E = cfg_E(fp64, M, kind);
     // the persistent kernel widens every tile to 512 threads (PassCfg with NTHR = 512)
     P.C = p->persistent ? std::max(1, kPersistThreads / (M / P.E)) : cfg_C(fp64, M, kind);
-    if (cfg_CP(fp64, M, kind) == 0 && !p->persistent && p->scheme == TFFT_SCHEME_BLOCK && (Guser == 0 || Guser == 64))
-        P.C = cfg_wide_C(M);
     P.stages = n_stages(M, P.E);
     const int G0 = Guser > 0 ? Guser : (kind == KIND_ROWS ? default_group(M) : 64);
     int64_t tiles;  // workgroup iterations of the pass
@@ -232,6 +230,13 @@ int shape_pass(tfft_plan_s *p, int idx, int M, int kind, int Guser, int grid_sca
             P.n_outer = p->batch;
             n_sub = P.rows;
         }
+        // the column kernel's strips, where there are outer units for groups of
+        // 64 (a batch of one has them smaller: complex64 N = 2^19, one signal,
+        // 20.99 us in narrow strips, 21.47 in wide ones)
+        const int wide = cfg_wide_C(M);
+        if (cfg_CP(fp64, M, kind) == 0 && !p->persistent && p->scheme == TFFT_SCHEME_BLOCK && (Guser == 0 || Guser == 64) &&
+            P.n_outer >= 64 / wide)
+            P.C = wide;
         if (n_sub % P.C != 0) return TFFT_E_UNSUPPORTED;
         P.rb = (int)std::max<int64_t>(1, std::min<int64_t>(std::max(1, G0 / P.C), P.n_outer));
         P.G = P.C * P.rb;
