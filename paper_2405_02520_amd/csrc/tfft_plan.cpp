@@ -1282,7 +1282,27 @@ int ragged_launch_branches(tfft_ragged_s *r, const void *d_in, void *d_out, int 
     return rc;
 }
 
-constexpr int64_t kPItemTiles = 32;  // default tiles per work item
+// Tiles per work item: about a workgroup's share of one pass over the batch,
+// rounded up to a power of two.  More leaves CUs idle while the rest walk long
+// items, and a pass waits for the longest; beyond 16 nothing is left to save on
+// an item's start, and below 4 its start dominates.  Measured (us, 32 tiles
+// before, then 4 - 8 - 16): complex64, 100 signals of 2^10..2^18 points (6 tiles
+// per CU) 311, 172 - 153 - 202; 20 of 2^8..2^16 (below 1) 284, 105 - 133 - 196;
+// 1024 of 2^6..2^20 (180) 1875, 2152 - 1917 - 1832; complex128, 300 of 2^6..2^18
+// (12) 496, 351 - 336 - 335.
+int64_t persist_item_tiles(const tfft_ragged_s *r) {
+    int cus = 0, dev = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    int64_t tiles = 0;
+    for (const auto &c : r->classes) {
+        const PassPlan &P = c.plan->pass[0];
+        tiles += P.n_groups * std::max(1, P.G / std::max(1, P.C));
+    }
+    int64_t t = 4;
+    while (t < 16 && t * std::max(1, cus) < tiles) t *= 2;
+    return t;
+}
 
 // Signals per dependency chunk of a class: a multiple of the signals every
 // pass's checksum group spans (so that no group straddles two chunks), at
@@ -1351,10 +1371,9 @@ int persist_build(tfft_ragged_s *r) {
     }
     r->n_done = nd;
     std::vector<int32_t> need((size_t)std::max(1, nd), 0);
-    // tiles per item: as tuned, else 32 (an item's start, with its first
-    // load not overlapped, then costs a few percent of its work); items keep
-    // whole groups, at most kPSlotCap of them
-    const int64_t target = r->item_tiles > 0 ? r->item_tiles : kPItemTiles;
+    // tiles per item: as tuned, else by the batch; items keep whole groups, at
+    // most kPSlotCap of them
+    const int64_t target = r->item_tiles > 0 ? r->item_tiles : persist_item_tiles(r);
     // items per task, in chunk order
     std::vector<std::vector<PItem>> per(ntask);
     for (int t = 0; t < ntask; ++t) {
