@@ -18,6 +18,14 @@ namespace tfft {
 // The last pass reads rows, so its first stage has the lanes along the
 // positions; its exchange turns the tile, and the outputs leave with the lanes
 // along the members, which is the transposed store.
+//
+// Bound by HBM (16 bytes per element and pass) and, with the checksum, close to
+// it by instruction issue.  128 registers, so that 16 wavefronts per CU hide
+// each other's exchanges with the next tile's loads in flight, where the pass
+// kernels hold 190-240 and 8.  Measured at 1 GiB, FT CORRECT, us of the first and
+// the last pass, pass kernels then columns: N = 2^13 531 + 535 -> 432 + 464 (4.0
+// -> 4.8 TB/s), 2^17 605 + 540 -> 541 + 490; N = 2^19 first pass (M = 512) 670 ->
+// 545; N = 2^19 with the checksum off 629 -> 509 in all.
 template <typename R, int M, int KIND, int FT>
 struct ColCfg {
     static constexpr bool BLK = FT == FT_BLOCK;
@@ -64,6 +72,9 @@ __global__ void __launch_bounds__(cfg_col_threads(M)) col_kernel(PassArgs args) 
     using Cf = ColCfg<R, M, KIND, FT>;
     constexpr bool BLK = Cf::BLK;
     constexpr int E = Cf::E, T = Cf::T, WV = Cf::WV, C = Cf::C, NSTAGE = Cf::NSTAGE, MB = Cf::MB, PW = Cf::PW;
+    // the next tile's loads ahead; not where the fault hook leaves no registers for
+    // them (the strided passes of 256 and 512 points would spill in every tile)
+    constexpr bool AHEAD = !(HOOK && KIND == KIND_STRIDED && M >= 256);
     using St = Stages<M, E>;
     __shared__ __align__(16) cx<R> lds[Cf::NBUF][M * MB];
     __shared__ double red[BLK ? Cf::NSUM : 1][BLK ? WV : 1][64];
@@ -242,7 +253,7 @@ __global__ void __launch_bounds__(cfg_col_threads(M)) col_kernel(PassArgs args) 
     int g = blockIdx.x;
     if (nwg % 8 == 0) g = (int)(blockIdx.x % 8) * (nwg / 8) + (int)(blockIdx.x / 8);
     int it = 0;
-    load_tile(g, 0);
+    if constexpr (AHEAD) load_tile(g, 0);
     const int n_groups = (int)k->n_groups;
     for (; g < n_groups; g += nwg) {
         asm volatile("" : "+s"(k));
@@ -276,6 +287,7 @@ __global__ void __launch_bounds__(cfg_col_threads(M)) col_kernel(PassArgs args) 
                 twA = itw(*k, ((uint32_t)j * i) & mask);
                 twB = itw(*k, ((uint32_t)T * i) & mask);
             }
+            if constexpr (!AHEAD) load_tile(g, r);
             cx<R> d[E];
 #pragma unroll
             for (int m = 0; m < E; ++m) {
@@ -284,7 +296,7 @@ __global__ void __launch_bounds__(cfg_col_threads(M)) col_kernel(PassArgs args) 
                 asm volatile("" : "+v"(d[m].re), "+v"(d[m].im));
             }
             asm volatile("" ::: "memory");
-            load_tile(r + 1 < Cf::ROUNDS ? g : g + nwg, r + 1 < Cf::ROUNDS ? r + 1 : 0);
+            if constexpr (AHEAD) load_tile(r + 1 < Cf::ROUNDS ? g : g + nwg, r + 1 < Cf::ROUNDS ? r + 1 : 0);
 
             if constexpr (BLK) {
                 double lr = 0.0, li = 0.0, sv = 0.0;

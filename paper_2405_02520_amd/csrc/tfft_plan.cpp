@@ -527,8 +527,11 @@ bool use_tiles(const tfft_plan_s *p) {
     return small || few;
 }
 
-// Whether a pass runs in the column kernel: complex64, whole groups of 64
-// members in its strip width.
+// Whether a pass runs in the column kernel: complex64, 64..512 points, whole
+// groups of 64 members in its strip width (a lane per member).  Strided and last
+// passes gain 10-20% (tfft_cols.h); a last pass of 1024 points has 8 members per
+// tile and is 1.6 times slower in this form, and complex128 has no registers
+// left for it (32 for a tile and 32 for the next).
 bool use_cols(const tfft_plan_s *p, const PassPlan &P) {
     return cfg_cols(p->dtype == TFFT_C128, P.M, P.kind) && P.G == 64 && P.C == cfg_wide_C(P.M) && !p->persistent &&
            std::max(P.n_groups, P.n_outer) < (int64_t(1) << 30);
