@@ -150,9 +150,19 @@ def kernel_source_sha():
     """Hash of the device code and its compile-time configuration (the
     kernel templates, their dispatch and the configuration header)."""
     h = hashlib.sha256()
-    for f in ("tfft_kernels.h", "tfft_kernels.hip", "tfft_internal.h"):
+    for f in ("tfft_kernels.h", "tfft_cols.h", "tfft_kernels.hip", "tfft_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_2405_02520_amd", "csrc", f), "rb").read())
     return h.hexdigest()
+
+
+def kernel_name(dt, M, kind, ft):
+    """The kernel that a pass of the sweep's batches runs in."""
+    R, code, on = ("float" if dt == "c64" else "double"), {"rows": 0, "strided": 1, "last": 2}[kind], int(ft != "off")
+    if dt == "c64" and kind != "rows" and 64 <= M <= 512:
+        return f"col_kernel<{R}, {M}, {code}, {on}, false, false>"
+    if kind == "rows" and (512 <= M <= 4096 if dt == "c64" else 256 <= M <= 2048):
+        return f"turn_kernel<{R}, {M}, {on}>"
+    return f"pass_kernel<{R}, {M}, {code}, {on}>"
 
 
 def pmc_traffic(kernel_key):
@@ -224,7 +234,7 @@ def summarize_pmc(root):
         if label == "copy" or "FETCH_SIZE" not in ctrs or "WRITE_SIZE" not in ctrs:
             continue
         for name in sorted(set(ctrs["FETCH_SIZE"]) & set(ctrs["WRITE_SIZE"])):
-            if "pass_kernel" not in name:
+            if not any(k in name for k in ("pass_kernel", "turn_kernel", "col_kernel")):
                 continue
             f = ctrs["FETCH_SIZE"][name]["FETCH_SIZE"] * 1024 * (scale["FETCH_SIZE"] or 1.0)
             w = ctrs["WRITE_SIZE"][name]["WRITE_SIZE"] * 1024 * (scale["WRITE_SIZE"] or 1.0)
@@ -666,9 +676,7 @@ def main():
                 dom = cand
     _, ddt, dk, dpass, dkind, dM, dalgo, dms = dom
     achieved = dalgo / (dms * 1e-3) / 1e9
-    kind_code = {"rows": 0, "strided": 1, "last": 2}[dkind]
-    kernel_key = (f"{ddt}_k{dk} void tfft::pass_kernel<{'float' if ddt == 'c64' else 'double'}, {dM}, {kind_code}, "
-                  f"{0 if args.ft == 'off' else 1}>(tfft::PassArgs)")
+    kernel_key = f"{ddt}_k{dk} void tfft::{kernel_name(ddt, dM, dkind, args.ft)}(tfft::PassArgs)"
     tr = pmc_traffic(kernel_key)
     if tr is not None:
         tr = tr["traffic_bytes"]
