@@ -12,26 +12,48 @@ corrected.
 """
 from __future__ import annotations
 
+import threading
+
 import torch
 
 from . import Plan
 
+# shape -> {stream handle: (forward plan, adjoint plan)}.  A plan must not run on
+# two streams at once (it owns its workspace, tickets and report), so every
+# stream has its own.
 _PLANS: dict = {}
+_LAST: dict = {}  # shape -> {"forward" | "backward": the plan that last executed}
+_LOCK = threading.Lock()  # the backward passes run on autograd's threads
 
 
-def _plans(n: int, batch: int, dtype, device) -> tuple[Plan, Plan]:
-    key = (n, batch, str(dtype), str(device))
-    if key not in _PLANS:
-        with torch.cuda.device(device):
-            _PLANS[key] = (Plan(n, batch, dtype), Plan(n, batch, dtype, inverse_unscaled=True))
-    return _PLANS[key]
+def _key(n: int, batch: int, dtype, device) -> tuple:
+    return (n, batch, str(dtype), str(device))
+
+
+def _plans(n: int, batch: int, dtype, device, stream=None) -> tuple[Plan, Plan]:
+    st = (stream if stream is not None else torch.cuda.current_stream(device)).cuda_stream
+    with _LOCK:
+        pairs = _PLANS.setdefault(_key(n, batch, dtype, device), {})
+        if st not in pairs:
+            with torch.cuda.device(device):
+                if pairs and torch.cuda.is_current_stream_capturing():
+                    # nothing can be allocated while a graph is captured: the
+                    # graph takes over the pair of the warm-up, and that stream
+                    # gets a new one when it next needs it
+                    pairs[st] = pairs.pop(next(reversed(pairs)))
+                else:
+                    pairs[st] = (Plan(n, batch, dtype), Plan(n, batch, dtype, inverse_unscaled=True))
+        return pairs[st]
 
 
 def clear_plan_cache() -> None:
-    for fwd, adj in _PLANS.values():
-        fwd.close()
-        adj.close()
-    _PLANS.clear()
+    with _LOCK:
+        for pairs in _PLANS.values():
+            for fwd, adj in pairs.values():
+                fwd.close()
+                adj.close()
+        _PLANS.clear()
+        _LAST.clear()
 
 
 class UncorrectableError(RuntimeError):
@@ -49,21 +71,27 @@ class _FFTFunction(torch.autograd.Function):
     def forward(ctx, x, ft_mode, check):
         n = x.shape[-1]
         batch = x.numel() // n
-        fwd, adj = _plans(n, batch, x.dtype, x.device)
-        ctx.adj = adj
+        st = torch.cuda.current_stream(x.device)
+        fwd, _ = _plans(n, batch, x.dtype, x.device, st)
         ctx.ft_mode = ft_mode
         ctx.check = check
         xc = x.contiguous()
-        y = fwd.forward(xc, ft_mode=ft_mode).view(x.shape)
+        y = fwd.forward(xc, ft_mode=ft_mode, stream=st).view(x.shape)
+        _LAST.setdefault(_key(n, batch, x.dtype, x.device), {})["forward"] = fwd
         if check and ft_mode == "correct":
             _verify(fwd, "forward transform")
         return y
 
     @staticmethod
     def backward(ctx, gy):
-        gx = ctx.adj.inverse(gy.contiguous(), ft_mode=ctx.ft_mode)
+        n = gy.shape[-1]
+        st = torch.cuda.current_stream(gy.device)
+        batch = gy.numel() // n
+        _, adj = _plans(n, batch, gy.dtype, gy.device, st)
+        gx = adj.inverse(gy.contiguous(), ft_mode=ctx.ft_mode, stream=st)
+        _LAST.setdefault(_key(n, batch, gy.dtype, gy.device), {})["backward"] = adj
         if ctx.check and ctx.ft_mode == "correct":
-            _verify(ctx.adj, "backward transform")
+            _verify(adj, "backward transform")
         return gx.view(gy.shape), None, None
 
 
@@ -83,8 +111,11 @@ def fft(x: torch.Tensor, ft_mode: str = "correct", check: bool = False) -> torch
 
 
 def last_reports():
-    """Reports of the most recent forward and backward executions of each cached plan."""
-    out = {}
-    for key, (fwd, adj) in _PLANS.items():
-        out[key] = {"forward": fwd.report(), "backward": adj.report()}
-    return out
+    """Reports of the most recent forward and backward executions of each shape
+    (length, batch, dtype, device)."""
+    with _LOCK:
+        last = {}
+        for key, pairs in _PLANS.items():
+            for fwd, adj in pairs.values():
+                last[key] = {"forward": fwd, "backward": adj, **_LAST.get(key, {})}
+    return {key: {way: plan.report() for way, plan in ways.items()} for key, ways in last.items()}
