@@ -429,8 +429,7 @@ constexpr int kTickStride = 32;  // tickets a 128-byte line apart: atomics on on
 struct TileArgs {
     double *part;        // [n_groups << split_log2][5] partial group sums
     uint32_t *tick;      // [n_groups * kTickStride] parts of the group done, 0 between launches
-    int32_t *state;      // [n_groups] 1 for a group flagged in this execution, else 0
-    int64_t rec0;        // index of the pass's first group among the records
+    int64_t rec0;        // index of the pass's first group among the records (action 0: not flagged)
     int32_t split_log2;
     int32_t rounds;
     int32_t fix;         // CORRECT mode

@@ -1718,9 +1718,9 @@ __global__ void __launch_bounds__(kCorrThreads) correct_kernel(PassArgs a) {
 // Its correction reads outputs of the other parts, so a group of several
 // parts stores its outputs through the caches (a release fence per workgroup
 // instead writes the XCD's whole L2 back: complex64 N = 1024, 2^20 elements
-// 45 us, through the caches 9).  State and record of a group have a place of
-// their own: nothing is counted, so nothing is reset between executions, and
-// one launch per pass does everything.
+// 45 us, through the caches 9).  A group's record has a place of its own, with
+// action 0 where the group is clean: nothing is counted, so nothing is reset
+// between executions, and one launch per pass does everything.
 template <typename R, int M, int KIND, int FT>
 __global__ void __launch_bounds__(cfg_tile_threads(sizeof(R) == 8, M, KIND)) tile_kernel(PassArgs a, TileArgs t) {
     using Cf = PassCfg<R, M, KIND, FT, 0, true>;
@@ -1743,7 +1743,7 @@ __global__ void __launch_bounds__(cfg_tile_threads(sizeof(R) == 8, M, KIND)) til
                                        PassHooks{nullptr, nullptr, 0}, r * t.rounds, (r + 1) * t.rounds, sums,
                                        split && t.fix);
     if constexpr (FT == FT_NONE) {
-        if (r == 0 && tid == 0) t.state[g] = 0;
+        if (r == 0 && tid == 0) a.recs[t.rec0 + g].action = 0;
     } else {
         if (split && t.fix) vm_wait_all();  // every wavefront's outputs before the ticket
         __syncthreads();
@@ -1773,7 +1773,7 @@ __global__ void __launch_bounds__(cfg_tile_threads(sizeof(R) == 8, M, KIND)) til
                     DevRecord rc;
                     bad = decide_group<KIND, Cf::CP>(a, s, g, rc);
                     if (bad) a.recs[t.rec0 + g] = rc;
-                    t.state[g] = bad;
+                    else a.recs[t.rec0 + g].action = 0;
                 }
                 flagged = bad;
             }

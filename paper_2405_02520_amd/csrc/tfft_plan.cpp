@@ -115,7 +115,7 @@ struct tfft_plan_s {
     int persistent = 0;          // shaped for the persistent ragged kernel (tiles of 512 threads)
     int grid_scale = 0;
     int tile = 0;                // runs as tile launches (use_tiles)
-    void *d_tile = nullptr;      // tile launches, one allocation: tickets and states, partial sums
+    void *d_tile = nullptr;      // shared groups, one allocation: tickets, partial sums
 };
 
 namespace {
@@ -768,8 +768,8 @@ int shape_plan(tfft_plan_s *p, int64_t n, int64_t batch, int dtype, const tfft_o
     return TFFT_OK;
 }
 
-// The memory of tile launches and of shared groups: the tickets (shared by the passes, which run one
-// after the other, and zero between launches), every pass's group states, the
+// The memory of groups that several workgroups share: the tickets (shared by the
+// passes, which run one after the other, and zero between launches) and the
 // partial sums (shared as well).
 int tile_buffers(tfft_plan_s *p) {
     int64_t parts = 0, groups = 0, all = 0;
@@ -778,26 +778,24 @@ int tile_buffers(tfft_plan_s *p) {
         P.tile.split_log2 = p->tile ? tile_split_log2(p, P) : P.split_log2;
         P.tile.rounds = p->tile ? tile_rounds(p, P) >> P.tile.split_log2 : 0;
         P.tile.rec0 = all;
-        parts = std::max(parts, P.n_groups << P.tile.split_log2);
-        if (P.tile.split_log2 > 0) groups = std::max(groups, P.n_groups);
+        if (P.tile.split_log2 > 0) {
+            parts = std::max(parts, P.n_groups << P.tile.split_log2);
+            groups = std::max(groups, P.n_groups);
+        }
         all += P.n_groups;
     }
+    if (groups == 0) return TFFT_OK;
     const size_t tick_bytes = sizeof(uint32_t) * kTickStride * (size_t)groups;
-    const size_t state_bytes = (sizeof(int32_t) * (size_t)all + 255) / 256 * 256;
-    if (hipMalloc(&p->d_tile, tick_bytes + state_bytes + sizeof(double) * 5 * (size_t)parts) != hipSuccess) {
+    if (hipMalloc(&p->d_tile, tick_bytes + sizeof(double) * 5 * (size_t)parts) != hipSuccess) {
         p->d_tile = nullptr;
         return TFFT_E_NOMEM;
     }
-    // (a copy, unlike a memset, is complete when it returns: the first
-    // execution may be on a stream that does not wait for the null stream)
-    const std::vector<char> zero(tick_bytes + state_bytes, 0);
+    const std::vector<char> zero(tick_bytes, 0);  // (a copy: as for the report)
     if (hipMemcpy(p->d_tile, zero.data(), zero.size(), hipMemcpyHostToDevice) != hipSuccess) return TFFT_E_HIP;
-    char *base = static_cast<char *>(p->d_tile);
     for (int i = 0; i < p->passes; ++i) {
         TileArgs &T = p->pass[i].tile;
-        T.tick = reinterpret_cast<uint32_t *>(base);
-        T.state = reinterpret_cast<int32_t *>(base + tick_bytes) + T.rec0;
-        T.part = reinterpret_cast<double *>(base + tick_bytes + state_bytes);
+        T.tick = static_cast<uint32_t *>(p->d_tile);
+        T.part = reinterpret_cast<double *>(static_cast<char *>(p->d_tile) + tick_bytes);
     }
     return TFFT_OK;
 }
@@ -842,14 +840,21 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
             rc = TFFT_E_NOMEM;
         }
     }
+    p->tile = use_tiles(p);
     if (rc == TFFT_OK) {
+        const size_t rec_bytes = sizeof(DevRecord) * (size_t)p->rec_cap;
+        const DevReport zero{};
+        // tile launches: no group flagged before the first execution.  (The
+        // copy, unlike the memset, is complete when it returns, and with it the
+        // memset before it: the first execution may be on a stream that does
+        // not wait for the null stream)
         if (hipMalloc((void **)&p->d_rep, sizeof(DevReport)) != hipSuccess ||
-            hipMalloc((void **)&p->d_recs, sizeof(DevRecord) * (size_t)p->rec_cap) != hipSuccess)
+            hipMalloc((void **)&p->d_recs, rec_bytes) != hipSuccess)
             rc = TFFT_E_NOMEM;
-        else if (hipMemset(p->d_rep, 0, sizeof(DevReport)) != hipSuccess)
+        else if ((p->tile && hipMemset(p->d_recs, 0, rec_bytes) != hipSuccess) ||
+                 hipMemcpy(p->d_rep, &zero, sizeof(zero), hipMemcpyHostToDevice) != hipSuccess)
             rc = TFFT_E_HIP;
     }
-    p->tile = use_tiles(p);
     bool split = false;
     for (int i = 0; i < p->passes && !p->tile; ++i) {
         PassPlan &P = p->pass[i];
@@ -870,25 +875,13 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
 }
 
 // The report of an execution as tile launches: the flagged groups' records
-// and the counters they add up to.
+// (action not 0) and the counters they add up to.
 int read_tile_report(const tfft_plan_s *p, DevReport *h, std::vector<DevRecord> *recs) {
     *h = DevReport{};
-    const TileArgs &last = p->pass[p->passes - 1].tile;
-    const size_t all = (size_t)(last.rec0 + p->pass[p->passes - 1].n_groups);
-    std::vector<int32_t> state(all);
-    if (hipMemcpy(state.data(), p->pass[0].tile.state, sizeof(int32_t) * all, hipMemcpyDeviceToHost) != hipSuccess)
+    recs->resize((size_t)p->rec_cap);
+    if (hipMemcpy(recs->data(), p->recs_last, sizeof(DevRecord) * recs->size(), hipMemcpyDeviceToHost) != hipSuccess)
         return TFFT_E_HIP;
-    // consecutive flagged groups in one copy
-    for (size_t i = 0; i < all; ++i) {
-        if (!state[i]) continue;
-        size_t e = i + 1;
-        while (e < all && state[e]) ++e;
-        const size_t at = recs->size();
-        recs->resize(at + (e - i));
-        if (hipMemcpy(recs->data() + at, p->recs_last + i, sizeof(DevRecord) * (e - i), hipMemcpyDeviceToHost) != hipSuccess)
-            return TFFT_E_HIP;
-        i = e;
-    }
+    recs->erase(std::remove_if(recs->begin(), recs->end(), [](const DevRecord &r) { return r.action == 0; }), recs->end());
     h->n_flag = recs->size();
     for (const DevRecord &r : *recs) {
         h->corrected += r.action == TFFT_ACT_CORRECTED;
@@ -972,8 +965,8 @@ int tfft_exec_inverse(tfft_plan p, const void *d_in, void *d_out, int ft_mode, v
 
 // The same execution with its report and workspace in the static scratch:
 // [report counters | records | workspace], each part 256-byte aligned.  No
-// allocation of any kind; the counters are cleared by the reset kernel of
-// the execution itself.
+// allocation of any kind; the execution itself clears the counters (reset
+// kernel) or writes every group's record (tile launches).
 int tfft_exec_noalloc(tfft_plan p, const void *d_in, void *d_out, int ft_mode, int inverse, void *hip_stream) {
     if (!p) return TFFT_E_INVALID;
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
