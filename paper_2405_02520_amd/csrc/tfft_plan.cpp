@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -115,10 +116,13 @@ struct tfft_plan_s {
     int persistent = 0;          // shaped for the persistent ragged kernel (tiles of 512 threads)
     int grid_scale = 0;
     int tile = 0;                // runs as tile launches (use_tiles)
+    std::mutex gather_mu;        // tile launches: reports gathered behind the records, one at a time
     void *d_tile = nullptr;      // shared groups, one allocation: tickets, partial sums
 };
 
 namespace {
+
+constexpr int64_t kGatherRecords = 4096;  // 320 KiB
 
 int ilog2_64(int64_t x) {
     int k = 0;
@@ -843,13 +847,16 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
     p->tile = use_tiles(p);
     if (rc == TFFT_OK) {
         const size_t rec_bytes = sizeof(DevRecord) * (size_t)p->rec_cap;
+        // tile launches: behind the records what read_tile_report gathers
+        const size_t gather_bytes =
+            p->tile ? sizeof(DevReport) + sizeof(DevRecord) * (size_t)std::min(kGatherRecords, p->rec_cap) : 0;
         const DevReport zero{};
         // tile launches: no group flagged before the first execution.  (The
         // copy, unlike the memset, is complete when it returns, and with it the
         // memset before it: the first execution may be on a stream that does
         // not wait for the null stream)
         if (hipMalloc((void **)&p->d_rep, sizeof(DevReport)) != hipSuccess ||
-            hipMalloc((void **)&p->d_recs, rec_bytes) != hipSuccess)
+            hipMalloc((void **)&p->d_recs, rec_bytes + gather_bytes) != hipSuccess)
             rc = TFFT_E_NOMEM;
         else if ((p->tile && hipMemset(p->d_recs, 0, rec_bytes) != hipSuccess) ||
                  hipMemcpy(p->d_rep, &zero, sizeof(zero), hipMemcpyHostToDevice) != hipSuccess)
@@ -874,20 +881,30 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
     return TFFT_OK;
 }
 
-// The report of an execution as tile launches: the flagged groups' records
-// (action not 0) and the counters they add up to.
-int read_tile_report(const tfft_plan_s *p, DevReport *h, std::vector<DevRecord> *recs) {
-    *h = DevReport{};
-    recs->resize((size_t)p->rec_cap);
-    if (hipMemcpy(recs->data(), p->recs_last, sizeof(DevRecord) * recs->size(), hipMemcpyDeviceToHost) != hipSuccess)
-        return TFFT_E_HIP;
-    recs->erase(std::remove_if(recs->begin(), recs->end(), [](const DevRecord &r) { return r.action == 0; }), recs->end());
-    h->n_flag = recs->size();
-    for (const DevRecord &r : *recs) {
-        h->corrected += r.action == TFFT_ACT_CORRECTED;
-        h->benign += r.action == TFFT_ACT_BENIGN;
-        h->uncorrectable += r.action == TFFT_ACT_UNCORRECTABLE;
-    }
+// The report of an execution as tile launches: the flagged groups' records and
+// the counters they add up to, gathered on the device (on the null stream, after
+// the caller's wait for the execution's), so that what is copied is the flagged
+// ones: all of them at once up to kGatherRecords, beyond by windows of as many
+// records.
+int read_tile_report(tfft_plan_s *p, DevReport *h, std::vector<DevRecord> *recs) {
+    std::lock_guard<std::mutex> lock(p->gather_mu);
+    DevReport *cnt = reinterpret_cast<DevReport *>(p->d_recs + p->rec_cap);
+    DevRecord *out = reinterpret_cast<DevRecord *>(cnt + 1);
+    const int64_t cap = std::min(kGatherRecords, p->rec_cap);
+    auto gather = [&](int64_t at, int64_t n, DevReport *c) -> bool {
+        if (launch_reset(cnt, nullptr) != hipSuccess ||
+            launch_gather(p->recs_last + at, n, cnt, out, cap, nullptr) != hipSuccess ||
+            hipMemcpy(c, cnt, sizeof(*c), hipMemcpyDeviceToHost) != hipSuccess)
+            return false;
+        if (c->n_flag == 0 || (int64_t)c->n_flag > cap) return true;
+        const size_t k = recs->size();
+        recs->resize(k + (size_t)c->n_flag);
+        return hipMemcpy(recs->data() + k, out, sizeof(DevRecord) * (size_t)c->n_flag, hipMemcpyDeviceToHost) == hipSuccess;
+    };
+    if (!gather(0, p->rec_cap, h)) return TFFT_E_HIP;
+    DevReport part;
+    for (int64_t at = 0; (int64_t)h->n_flag > cap && at < p->rec_cap; at += cap)
+        if (!gather(at, std::min(cap, p->rec_cap - at), &part)) return TFFT_E_HIP;
     return TFFT_OK;
 }
 

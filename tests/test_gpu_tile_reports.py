@@ -76,3 +76,37 @@ def test_captured_but_never_run_reports_nothing(tf):
             plan.forward(x, ft_mode="detect")
             assert plan.report()[0]["detected"] == 1
             x[3, 5] = 1.0
+
+
+# (flagged groups, one in `every` of 10000 groups of 64 signals): one gather and
+# its edges, and beyond it by windows
+@pytest.mark.parametrize("flagged", [1, 4095, 4096, 4097, 9999])
+def test_scattered_records_come_whole_and_quickly(tf, flagged):
+    import time
+
+    import torch
+
+    groups, n = 10000, 4
+    x = torch.from_numpy(inputs.uniform(9520, 64 * groups, n, np.complex64)).cuda()
+    rng = inputs.fault_rng(flagged)
+    sets = {"scattered": np.sort(rng.permutation(groups)[:flagged]), "in a row": np.arange(flagged)}
+    best = {}
+    with tf.Plan(n, 64 * groups, "c64") as plan:
+        assert plan.info()["groups"] == [groups]
+        for name, hit in sets.items():
+            bad = x.clone()
+            bad[torch.from_numpy(64 * hit + hit % 64).cuda(), 1] = float("nan")
+            plan.forward(bad, ft_mode="detect")
+            c, r = plan.report()
+            assert c["detected"] == c["n_records"] == flagged and c["dropped"] == 0, c
+            assert [v.group for v in r] == list(hit) and all(v.action == "detected" for v in r)
+            best[name] = float("inf")
+            for _ in range(5):
+                t0 = time.perf_counter()
+                plan.report(cap=0)
+                best[name] = min(best[name], time.perf_counter() - t0)
+        plan.forward(x, ft_mode="detect")
+        assert plan.report()[0]["detected"] == 0
+    print(f"{flagged}: {best}", flush=True)
+    # one copy per run of flagged groups took 20 us each
+    assert best["scattered"] <= 5 * best["in a row"] + 1e-3
