@@ -155,14 +155,17 @@ def kernel_source_sha():
     return h.hexdigest()
 
 
-def kernel_name(dt, M, kind, ft):
-    """The kernel that a pass of the sweep's batches runs in."""
+def kernel_name(dt, n, batch, i, M, kind, ft):
+    """The kernel that pass i of a plan's executions runs in."""
+    import paper_2405_02520_amd as tf
+
     R, code, on = ("float" if dt == "c64" else "double"), {"rows": 0, "strided": 1, "last": 2}[kind], int(ft != "off")
-    if dt == "c64" and kind != "rows" and 64 <= M <= 512:
+    form = tf.forms(n, batch, dt, ft_mode=ft)[i]
+    if form == "columns":
         return f"col_kernel<{R}, {M}, {code}, {on}, false, false>"
-    if kind == "rows" and (512 <= M <= 4096 if dt == "c64" else 256 <= M <= 2048):
+    if form == "turns":
         return f"turn_kernel<{R}, {M}, {on}>"
-    return f"pass_kernel<{R}, {M}, {code}, {on}>"
+    return f"{form}_kernel<{R}, {M}, {code}, {on}>"
 
 
 def pmc_traffic(kernel_key):
@@ -676,7 +679,7 @@ def main():
                 dom = cand
     _, ddt, dk, dpass, dkind, dM, dalgo, dms = dom
     achieved = dalgo / (dms * 1e-3) / 1e9
-    kernel_key = f"{ddt}_k{dk} void tfft::{kernel_name(ddt, dM, dkind, args.ft)}(tfft::PassArgs)"
+    kernel_key = f"{ddt}_k{dk} void tfft::{kernel_name(ddt, 1 << dk, (1 << log2e[ddt]) >> dk, dpass, dM, dkind, args.ft)}(tfft::PassArgs)"
     tr = pmc_traffic(kernel_key)
     if tr is not None:
         tr = tr["traffic_bytes"]

@@ -293,6 +293,21 @@ int tfft_plan_info(tfft_plan p, tfft_plan_desc *info);
  * checksum groups and the workspace size. */
 int tfft_plan_describe(int64_t n, int64_t batch, int dtype, const tfft_options *opt, tfft_plan_desc *info);
 
+/* Launch form of a pass: which kernel a pass of a plan runs in.
+ *  PASS     one workgroup per checksum group, a grid-stride walk over the groups;
+ *  TILE     a group's tiles split over workgroups, correction in the same launch;
+ *  COLUMNS  one lane per member of a 64-member group;
+ *  TURNS    as PASS, with groups shared between workgroups or begun at a signal of
+ *           the workgroup's own. */
+enum tfft_form { TFFT_FORM_PASS = 0, TFFT_FORM_TILE = 1, TFFT_FORM_COLUMNS = 2, TFFT_FORM_TURNS = 3 };
+
+/* The launch forms of a plan created with these arguments on the current
+ * device, executed in ft_mode: forms[TFFT_MAX_PASSES] receives enum tfft_form of
+ * each pass, -1 beyond the last.  Computed on the host without creating the
+ * plan; validation as tfft_plan_describe.  (Without a device, groups that would be
+ * shared to fill it are taken as whole.) */
+int tfft_plan_forms(int64_t n, int64_t batch, int dtype, const tfft_options *opt, int ft_mode, int32_t *forms);
+
 /* Host generators of the tables a plan uploads (no device call):
  *  tfft_host_root: out[0] + i out[1] = w_n^t = exp(-2 pi i t / n) in binary64,
  *    for any integer t and n >= 1, the twiddle of the DFT matrix (Section II;

@@ -43,6 +43,7 @@ SCHEME_BLOCK, SCHEME_SIGNAL, SCHEME_THREAD = 0, 1, 2
 _SCHEMES = {"block": SCHEME_BLOCK, "signal": SCHEME_SIGNAL, "thread": SCHEME_THREAD}
 ACTION_NAMES = {ACT_DETECTED: "detected", ACT_CORRECTED: "corrected", ACT_BENIGN: "benign",
                 ACT_UNCORRECTABLE: "uncorrectable"}
+FORM_NAMES = {0: "pass", 1: "tile", 2: "columns", 3: "turns"}
 _MODES = {"off": FT_OFF, "detect": FT_DETECT, "correct": FT_CORRECT}
 
 
@@ -114,6 +115,8 @@ _sig = {
                          ctypes.c_int),
     "tfft_plan_describe": ([ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.POINTER(tfft_options),
                             ctypes.POINTER(tfft_plan_desc)], ctypes.c_int),
+    "tfft_plan_forms": ([ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.POINTER(tfft_options), ctypes.c_int,
+                         ctypes.POINTER(ctypes.c_int32)], ctypes.c_int),
     "tfft_host_root": ([ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(ctypes.c_double)], ctypes.c_int),
     "tfft_host_checksum_vector": ([ctypes.c_int64, ctypes.c_int, ctypes.c_double, ctypes.POINTER(ctypes.c_double)],
                                   ctypes.c_int),
@@ -425,6 +428,19 @@ def describe(n: int, batch: int, dtype="c64", group: int = 0, kappa: float = 0.0
     _check(tfft_plan_describe(int(n), int(batch), _dtype_code(dtype), ctypes.byref(opt), ctypes.byref(d)),
            "tfft_plan_describe")
     return _desc_dict(d)
+
+
+def forms(n: int, batch: int, dtype="c64", group: int = 0, passes: int = 0, grid_scale: int = 0, scheme="block",
+          chunk: int = 0, split: int = 0, ft_mode="correct") -> list:
+    """The launch form of each pass of a plan with these arguments ("pass",
+    "tile", "columns" or "turns"; see ``tfft_plan_forms``)."""
+    sch = _SCHEMES[scheme] if isinstance(scheme, str) else int(scheme)
+    opt = tfft_options(group=int(group), passes=int(passes), grid_scale=int(grid_scale), scheme=sch, chunk=int(chunk),
+                       split=int(split))
+    out = (ctypes.c_int32 * MAX_PASSES)()
+    mode = _MODES[ft_mode] if isinstance(ft_mode, str) else int(ft_mode)
+    _check(tfft_plan_forms(int(n), int(batch), _dtype_code(dtype), ctypes.byref(opt), mode, out), "tfft_plan_forms")
+    return [FORM_NAMES[f] for f in out if f >= 0]
 
 
 def host_root(t: int, n: int) -> complex:

@@ -266,6 +266,10 @@ constexpr int cfg_pf_fence(int fp64, int M, int kind) {
 // at a signal of its own.  Shorter ones gain from neither and lost 2% to the
 // scalar registers it takes.
 constexpr bool cfg_turns(int fp64, int M, int kind) { return kind == KIND_ROWS && M >= (fp64 ? 256 : 512) && M <= 4096; }
+// Whether a rows pass (ft: FT_NONE or FT_BLOCK) runs in the turn kernel.
+constexpr bool takes_turns(int fp64, int M, int kind, int split_log2, int rot_mul) {
+    return cfg_turns(fp64, M, kind) && (split_log2 > 0 || rot_mul > 0);
+}
 constexpr int cfg_threads(int fp64, int M, int kind) { return cfg_C(fp64, M, kind) * (M / cfg_E(fp64, M, kind)); }
 // Prefetch of the next tile straight into a second LDS buffer
 // (global_load_lds_dwordx4: 16-byte elements, i.e. complex128) for tiles of

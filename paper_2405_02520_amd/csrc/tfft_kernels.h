@@ -1813,7 +1813,7 @@ template <typename R, int M, int KIND, int FT>
 static hipError_t launch_one(const PassArgs &a, int grid, hipStream_t st) {
     constexpr int NT = cfg_threads(sizeof(R) == 8, M, KIND);
     if constexpr (cfg_turns(sizeof(R) == 8, M, KIND) && (FT == FT_NONE || FT == FT_BLOCK)) {
-        if (a.split_log2 > 0 || a.rot_mul > 0) {
+        if (takes_turns(sizeof(R) == 8, M, KIND, a.split_log2, a.rot_mul)) {
             hipLaunchKernelGGL((turn_kernel<R, M, FT>), dim3(grid), dim3(NT), 0, st, a);
             return hipGetLastError();
         }

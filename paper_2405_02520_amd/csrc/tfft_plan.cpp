@@ -385,6 +385,24 @@ ChunkGeom chunk_geom(const tfft_plan_s *p, const PassPlan &P, int64_t c0, int64_
     return c;
 }
 
+// Workgroups of a rows pass that all begin at the first signal of their groups
+// stay a power of two of bytes apart for the whole pass and crowd the same
+// memory channels: neighbours begin a quarter of a group apart, and groups of
+// more than 512 KiB a tile apart in pairs.  Measured (us, 1 GiB, begun at the
+// first signal - quarters - a tile apart in pairs): complex64 (512 KiB) N = 1024
+// 275 - 207 - 212, N = 4096 285 - 215 - 221; complex128 N = 512 (512 KiB) 459 -
+// 414 - 425, N = 1024 (1 MiB) 418 - 436 - 423 and at 512 MiB 257 - 222 - 216.
+// Groups below 256 KiB gain nothing (complex64 N = 1024 in groups of 16: 116,
+// quarters 119), nor do tiles of 64 KiB (complex128 N = 4096 509, a tile apart in
+// pairs 517).
+int64_t group_bytes(const tfft_plan_s *p, const PassPlan &P) { return (int64_t)P.G * P.M * (p->dtype == TFFT_C128 ? 16 : 8); }
+int rot_mul(const tfft_plan_s *p, const PassPlan &P) {
+    const int64_t bytes = group_bytes(p, P);
+    if (P.kind != KIND_ROWS || bytes < (256 << 10) || bytes / P.G >= 65536) return 0;
+    return bytes > (512 << 10) ? 1 : std::max(1, (std::max(1, P.G / P.C) >> P.split_log2) / 4);
+}
+int rot_shift(const tfft_plan_s *p, const PassPlan &P) { return P.kind == KIND_ROWS && group_bytes(p, P) > (512 << 10) ? 1 : 0; }
+
 // Arguments of the launch of pass i over the signals described by cg (nb
 // signals from cin / cout, the caller's buffers from the chunk's first
 // signal, or the ragged offset table sig), with the plan's tables and the
@@ -432,22 +450,8 @@ PassArgs pass_args(const tfft_plan_s *p, int i, const ChunkGeom &cg, int64_t nb,
     A.split_log2 = P.split_log2;
     A.part = P.tile.part;
     A.tick = P.tile.tick;
-    if (P.kind == KIND_ROWS) {
-        // Workgroups that all begin at the first signal of their groups stay a
-        // power of two of bytes apart for the whole pass and crowd the same
-        // memory channels: neighbours begin a quarter of a group apart, and
-        // groups of more than 512 KiB a tile apart in pairs.  Measured (us,
-        // 1 GiB, begun at the first signal - quarters - a tile apart in pairs):
-        // complex64 (512 KiB) N = 1024 275 - 207 - 212, N = 4096 285 - 215 -
-        // 221; complex128 N = 512 (512 KiB) 459 - 414 - 425, N = 1024 (1 MiB)
-        // 418 - 436 - 423 and at 512 MiB 257 - 222 - 216.  Groups below 256 KiB
-        // gain nothing (complex64 N = 1024 in groups of 16: 116, quarters 119), nor
-        // do tiles of 64 KiB (complex128 N = 4096 509, a tile apart in pairs 517).
-        const int rounds = std::max(1, P.G / P.C) >> P.split_log2;
-        const int64_t bytes = (int64_t)P.G * P.M * (fp64 ? 16 : 8);
-        A.rot_mul = bytes < (256 << 10) || P.M * (fp64 ? 16 : 8) >= 65536 ? 0 : (bytes > (512 << 10) ? 1 : std::max(1, rounds / 4));
-        A.rot_shift = bytes > (512 << 10) ? 1 : 0;
-    }
+    A.rot_mul = rot_mul(p, P);
+    A.rot_shift = rot_shift(p, P);
     A.o_log2 = ilog2_64(P.O);
     A.n_groups = cg.n_groups;
     A.g_base = cg.g_base;
@@ -561,6 +565,26 @@ int pass_split_log2(const tfft_plan_s *p, const PassPlan &P) {
     return k;
 }
 
+// The launch forms of a shaped plan: tiles, or the workgroups that share a
+// group of its pass kernel.
+void choose_forms(tfft_plan_s *p) {
+    p->tile = use_tiles(p);
+    for (int i = 0; i < p->passes && !p->tile; ++i) p->pass[i].split_log2 = pass_split_log2(p, p->pass[i]);
+}
+
+int scheme_ft(const tfft_plan_s *p, int mode) {
+    if (mode == TFFT_FT_OFF) return FT_NONE;
+    return p->scheme == TFFT_SCHEME_SIGNAL ? FT_SIGNAL : (p->scheme == TFFT_SCHEME_THREAD ? FT_THREAD : FT_BLOCK);
+}
+
+// The kernel that pass P runs in (enum tfft_form).
+int pass_form(const tfft_plan_s *p, const PassPlan &P, int ft) {
+    if (p->tile) return TFFT_FORM_TILE;
+    if (ft > FT_BLOCK) return TFFT_FORM_PASS;
+    if (use_cols(p, P)) return TFFT_FORM_COLUMNS;
+    return takes_turns(p->dtype == TFFT_C128, P.M, P.kind, P.split_log2, rot_mul(p, P)) ? TFFT_FORM_TURNS : TFFT_FORM_PASS;
+}
+
 // Device buffers of one execution: the report counters, the records and the
 // multi-pass workspace (the plan's own, or parts of the static scratch).
 struct ExecBufs {
@@ -593,7 +617,6 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
     Guard guard(p->device);
     hipStream_t st = (hipStream_t)stream;
     const int fp64 = p->dtype == TFFT_C128;
-    const int ft = mode != TFFT_FT_OFF;
     const bool tile = p->tile != 0;
     if (!tile && launch_reset(rep, st) != hipSuccess) return TFFT_E_HIP;
     // one chunk (the whole batch) unless the plan chunks its multi-pass batch
@@ -601,9 +624,7 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
     const bool timed = p->timing != 0;
     const bool per_pass_events = timed && chunk >= p->batch;
     if (timed && hipEventRecord(p->ev[0], st) != hipSuccess) return TFFT_E_HIP;
-    const int scheme_ft = !ft ? FT_NONE
-                              : (p->scheme == TFFT_SCHEME_SIGNAL ? FT_SIGNAL
-                                                                 : (p->scheme == TFFT_SCHEME_THREAD ? FT_THREAD : FT_BLOCK));
+    const int kft = scheme_ft(p, mode);
     // (a tile launch corrects its own groups)
     const bool correct = mode == TFFT_FT_CORRECT && p->scheme != TFFT_SCHEME_THREAD && !tile;
     for (int64_t c0 = 0; c0 < p->batch; c0 += chunk) {
@@ -618,18 +639,21 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
             const PassPlan &P = p->pass[i];
             const ChunkGeom cg = chunk_geom(p, P, c0, nb);
             const PassArgs A = pass_args(p, i, cg, nb, cin, cout, work, sig, inverse, mode, rep, recs);
-            if (tile) {
+            const int form = pass_form(p, P, kft);
+            hipError_t e;
+            if (form == TFFT_FORM_TILE) {
                 TileArgs T = P.tile;
                 T.fix = mode == TFFT_FT_CORRECT;
-                if (launch_tile(fp64, P.M, P.kind, scheme_ft, A, T, st) != hipSuccess) return TFFT_E_HIP;
-            } else if (use_cols(p, P) && scheme_ft <= FT_BLOCK) {
+                e = launch_tile(fp64, P.M, P.kind, kft, A, T, st);
+            } else if (form == TFFT_FORM_COLUMNS) {
                 const int64_t most = p->grid_scale >= 0 ? (int64_t)TFFT_COL_GRID << p->grid_scale
                                                         : (int64_t)TFFT_COL_GRID >> -p->grid_scale;
                 const int grid = (int)std::min<int64_t>((cg.n_groups + 7) / 8 * 8, most * (P.M == 64 ? 2 : 1));
-                if (launch_cols(fp64, P.M, P.kind, scheme_ft, A, grid, st) != hipSuccess) return TFFT_E_HIP;
-            } else if (launch_pass(fp64, P.M, P.kind, scheme_ft, A, cg.grid, st) != hipSuccess) {
-                return TFFT_E_HIP;
+                e = launch_cols(fp64, P.M, P.kind, kft, A, grid, st);
+            } else {
+                e = launch_pass(fp64, P.M, P.kind, kft, A, cg.grid, st);
             }
+            if (e != hipSuccess) return TFFT_E_HIP;
             if (per_pass_events && hipEventRecord(p->ev[1 + 2 * i], st) != hipSuccess) return TFFT_E_HIP;
             if (correct) {
                 // one workgroup per possible record, at most TFFT_CORRECT_GRID; a workgroup
@@ -844,7 +868,7 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
             rc = TFFT_E_NOMEM;
         }
     }
-    p->tile = use_tiles(p);
+    choose_forms(p);
     if (rc == TFFT_OK) {
         const size_t rec_bytes = sizeof(DevRecord) * (size_t)p->rec_cap;
         // tile launches: behind the records what read_tile_report gathers
@@ -862,13 +886,7 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
                  hipMemcpy(p->d_rep, &zero, sizeof(zero), hipMemcpyHostToDevice) != hipSuccess)
             rc = TFFT_E_HIP;
     }
-    bool split = false;
-    for (int i = 0; i < p->passes && !p->tile; ++i) {
-        PassPlan &P = p->pass[i];
-        P.split_log2 = pass_split_log2(p, P);
-        split = split || P.split_log2 > 0;
-    }
-    if (rc == TFFT_OK && (p->tile || split)) rc = tile_buffers(p);
+    if (rc == TFFT_OK) rc = tile_buffers(p);
     if (rc == TFFT_OK && host_off) {
         std::vector<int64_t> off(host_off, host_off + batch);
         rc = upload(&p->d_sig_off, off);
@@ -1977,6 +1995,20 @@ int tfft_plan_describe(int64_t n, int64_t batch, int dtype, const tfft_options *
     if (!p) return TFFT_E_NOMEM;
     int rc = shape_plan(p, n, batch, dtype, opt, false);
     if (rc == TFFT_OK) rc = tfft_plan_info(p, info);
+    delete p;  // owns no device memory
+    return rc;
+}
+
+int tfft_plan_forms(int64_t n, int64_t batch, int dtype, const tfft_options *opt, int ft_mode, int32_t *forms) {
+    if (!forms || ft_mode < TFFT_FT_OFF || ft_mode > TFFT_FT_CORRECT) return TFFT_E_INVALID;
+    tfft_plan_s *p = new (std::nothrow) tfft_plan_s();
+    if (!p) return TFFT_E_NOMEM;
+    const int rc = shape_plan(p, n, batch, dtype, opt, false);
+    if (rc == TFFT_OK) {
+        (void)hipGetDevice(&p->device);
+        choose_forms(p);
+        for (int i = 0; i < kMaxPasses; ++i) forms[i] = i < p->passes ? pass_form(p, p->pass[i], scheme_ft(p, ft_mode)) : -1;
+    }
     delete p;  // owns no device memory
     return rc;
 }
