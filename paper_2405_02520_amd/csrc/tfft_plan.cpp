@@ -516,8 +516,9 @@ int tile_split_log2(const tfft_plan_s *p, const PassPlan &P) {
 // (complex128 N = 2^20 at 128 wavefronts 44 -> 36 / 38 -> 32, at 512 83 -> 106 /
 // 80 -> 73).  Signals of up to 16 points always run as tiles: their pass kernels
 // hold less than a wavefront per workgroup (complex64 N = 16 at 2^24 154 -> 85 /
-// 146 -> 79).  A plan with a grid_scale or a chunk of its own keeps the pass
-// kernels those describe.
+// 146 -> 79), up to the 2^32 - 1 threads of a launch (one workgroup per group,
+// where the pass kernels walk over the groups).  A plan with a grid_scale or a
+// chunk of its own keeps the pass kernels those describe.
 bool use_tiles(const tfft_plan_s *p) {
     if (p->persistent || p->scheme != TFFT_SCHEME_BLOCK || p->grid_scale != 0 || p->chunk < p->batch) return false;
     const int fp64 = p->dtype == TFFT_C128;
@@ -525,6 +526,7 @@ bool use_tiles(const tfft_plan_s *p) {
     for (int i = 0; i < p->passes; ++i) {
         const PassPlan &P = p->pass[i];
         if (tile_rounds(p, P) < 1) return false;
+        if ((P.n_groups + 7) / 8 * 8 * cfg_tile_threads(fp64, P.M, P.kind) > UINT32_MAX) return false;
         const int threads = cfg_threads(fp64, P.M, P.kind);
         int64_t limit = TFFT_TILE_MAX_WAVES;
         if (P.kind == KIND_ROWS && P.M >= 1024) limit = limit * (fp64 ? (P.M >= 4096 ? 4 : 3) : 1) / 4;

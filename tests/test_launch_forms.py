@@ -28,6 +28,10 @@ FORMS = [
     (dict(n=1 << 15, batch=1, passes=3), ["tile"] * 3),
     (dict(n=1 << 16, batch=3, passes=3, dtype="c128"), ["tile"] * 3),
     (dict(n=1 << 21, batch=1), ["pass", "columns", "pass"]),
+    # ... that a launch of one workgroup per group holds (less than 2^32 threads)
+    (dict(n=2, batch=(1 << 32) - 512), ["tile"]),
+    (dict(n=2, batch=(1 << 32) - 511), ["pass"]),
+    (dict(n=4, batch=1 << 32, dtype="c128"), ["pass"]),
     # not where the plan has a launch or a scheme of its own
     (dict(n=256, batch=64, grid_scale=1), ["pass"]),
     (dict(n=256, batch=64, scheme="signal"), ["pass"]),
