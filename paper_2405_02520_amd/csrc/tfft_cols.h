@@ -225,11 +225,12 @@ __global__ void __launch_bounds__(cfg_col_threads(M)) col_kernel(PassArgs args) 
         i = __builtin_amdgcn_readfirstlane(i);
         asm volatile("" : "+s"(i));  // its LDS addresses are formed here
         if (wv != ((i + 8) & (WV - 1)) || lane != 0) return;
-        // the threshold test in squares (sums of binary32 data: no overflow);
-        // the record's member is located by whoever reads it
+        // the threshold test in squares (sums of binary32 data: no overflow, and
+        // the host bounds the factor); the record's member is located by whoever
+        // reads it
         const double *s = fin[i & 1];
-        const double tc = k->tau_coef;
-        if (!(s[0] * s[0] + s[1] * s[1] <= tc * tc * s[4])) {
+        if (!(s[0] * s[0] + s[1] * s[1] <= k->tau_sq * s[4])) {
+            const double tc = k->tau_coef;
             const unsigned long long n = atomicAdd(&k->rep->n_flag, 1ULL);
             if ((int64_t)n < k->rec_cap) {
                 DevRecord *rc = k->recs + n;

@@ -425,6 +425,7 @@ struct PassArgs {
     int32_t rot_shift;
     const double *ckappa; // complex128 tile kernels, [M]: c_n = cf (1 + i ckappa_n)
     double cf_re, cf_im;
+    double tau_sq;      // column kernels: tau_coef^2, the factor within 1e-150..1e150
 };
 
 // What a tile launch needs besides PassArgs: a group's tiles are split over

@@ -470,6 +470,11 @@ PassArgs pass_args(const tfft_plan_s *p, int i, const ChunkGeom &cg, int64_t nb,
     A.itw_bits = p->itw_bits;
     A.pass = i;
     A.tau_coef = P.tau_coef * A.out_scale;  // the outputs' rounding noise scales with them
+    // Beyond these bounds the square over- or underflows, and no sums of binary32
+    // data (energies of 2e-90 to 1e82 or 0, residuals from 1e-61 on or 0) compare
+    // otherwise than within them.
+    const double bounded = std::min(std::max(A.tau_coef, 1e-150), 1e150);
+    A.tau_sq = bounded * bounded;
     A.rep = rep;
     A.recs = recs;
     A.rec_cap = p->rec_cap;
