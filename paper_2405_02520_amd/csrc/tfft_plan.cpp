@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <iterator>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -1328,6 +1329,9 @@ int ragged_launch_branches(tfft_ragged_s *r, const void *d_in, void *d_out, int 
 // per CU) 311, 172 - 153 - 202; 20 of 2^8..2^16 (below 1) 284, 105 - 133 - 196;
 // 1024 of 2^6..2^20 (180) 1875, 2152 - 1917 - 1832; complex128, 300 of 2^6..2^18
 // (12) 496, 351 - 336 - 335.
+// (The tuner's candidates; the rule chooses one of the first kItemTilesRule.)
+constexpr int64_t kItemTiles[] = {4, 8, 16, 32, 64, 128};
+constexpr int kItemTilesRule = 3;
 int64_t persist_item_tiles(const tfft_ragged_s *r) {
     int cus = 0, dev = 0;
     (void)hipGetDevice(&dev);
@@ -1337,9 +1341,9 @@ int64_t persist_item_tiles(const tfft_ragged_s *r) {
         const PassPlan &P = c.plan->pass[0];
         tiles += P.n_groups * std::max(1, P.G / std::max(1, P.C));
     }
-    int64_t t = 4;
-    while (t < 16 && t * std::max(1, cus) < tiles) t *= 2;
-    return t;
+    int i = 0;
+    while (i + 1 < kItemTilesRule && kItemTiles[i] * std::max(1, cus) < tiles) ++i;
+    return kItemTiles[i];
 }
 
 // Signals per dependency chunk of a class: a multiple of the signals every
@@ -1649,7 +1653,7 @@ int persist_tune(tfft_ragged_s *r, const void *d_in, void *d_out, hipStream_t st
         }
         set(bestv);
     };
-    pick({8, 16, 32, 64, 128}, [&](int64_t v) { r->item_tiles = v; });
+    pick(std::vector<int64_t>(std::begin(kItemTiles), std::end(kItemTiles)), [&](int64_t v) { r->item_tiles = v; });
     pick({0, 1}, [&](int64_t v) { r->item_interleave = (int)v; });
     pick({1, kPQueues}, [&](int64_t v) { r->n_queues = (int)v; });
     pick({8, 32}, [&](int64_t v) { r->chunk_div = (int)v; });
