@@ -71,11 +71,11 @@ struct PassPlan {
     int S = 1, O = 1, m1 = 1, m2 = 1;
     int grid = 0;
     void *d_stw = nullptr;       // element-type stage twiddles
-    double *d_stw64 = nullptr;   // fp64 stage twiddles
+    double *d_stw64 = nullptr;   // fp64 stage twiddles; behind them the next four
     double *d_cfwd = nullptr;    // checksum vector, forward
     double *d_cinv = nullptr;    // checksum vector, inverse (scaled for the last pass)
     double *d_cinv_unscaled = nullptr;
-    double *d_kappa = nullptr;   // tile kernels: checksum_kappa, forward then inverse
+    double *d_kappa = nullptr;   // complex128 tile kernels: kappa_n, forward then inverse
     int32_t *d_fault_head = nullptr;
     DevFault *d_faults = nullptr;
     double tau_coef = 0.0;
@@ -118,7 +118,6 @@ struct tfft_plan_s {
     int grid_scale = 0;
     int tile = 0;                // runs as tile launches (use_tiles)
     std::mutex gather_mu;        // tile launches: reports gathered behind the records, one at a time
-    void *d_tile = nullptr;      // shared groups, one allocation: tickets, partial sums
 };
 
 namespace {
@@ -162,26 +161,28 @@ int default_group(int M) {
 // Re v / Im v, which is what the tile kernels read.
 cd checksum_factor(int M) { return 0.5 * (1.0 - unit_root(M % 3, 3)); }
 
-std::vector<double> checksum_kappa(int M, bool inverse) {
-    std::vector<double> out((size_t)M);
+// v of every n.
+std::vector<cd> checksum_roots(int M, bool inverse) {
+    std::vector<cd> v((size_t)M);
     const int64_t M3 = 3 * (int64_t)M;
     for (int n = 0; n < M; ++n) {
         int64_t q = ((int64_t)M + (inverse ? -3 : 3) * (int64_t)n) % M3;
         if (q < 0) q += M3;
-        const cd v = unit_root(q, 2 * M3);
-        out[(size_t)n] = v.real() / v.imag();
+        v[(size_t)n] = unit_root(q, 2 * M3);
     }
-    return out;
+    return v;
 }
 
-std::vector<double> checksum_vec(int M, bool inverse, double scale) {
+void append_kappa(std::vector<double> *out, const std::vector<cd> &roots) {
+    for (const cd &v : roots) out->push_back(v.real() / v.imag());
+}
+
+std::vector<double> checksum_vec(const std::vector<cd> &roots, double scale) {
+    const int M = (int)roots.size();
     std::vector<double> out(2 * (size_t)M);
     const cd num = 1.0 - unit_root(M % 3, 3);
-    const int64_t M3 = 3 * (int64_t)M;
     for (int n = 0; n < M; ++n) {
-        int64_t q = ((int64_t)M + (inverse ? -3 : 3) * (int64_t)n) % M3;
-        if (q < 0) q += M3;
-        const cd v = unit_root(q, 2 * M3);
+        const cd v = roots[(size_t)n];
         const cd c = scale * num * std::conj(v) * cd(0.0, 1.0 / (2.0 * v.imag()));
         out[2 * n] = c.real();
         out[2 * n + 1] = c.imag();
@@ -288,15 +289,24 @@ int upload_pass(tfft_plan_s *p, int idx) {
         std::vector<float> w32(w64.begin(), w64.end());
         if ((rc = upload((float **)&P.d_stw, w32)) != TFFT_OK) return rc;
     }
-    if ((rc = upload(&P.d_stw64, w64)) != TFFT_OK) return rc;
-    if ((rc = upload(&P.d_cfwd, checksum_vec(M, false, 1.0))) != TFFT_OK) return rc;
-    if ((rc = upload(&P.d_cinv_unscaled, checksum_vec(M, true, 1.0))) != TFFT_OK) return rc;
-    if ((rc = upload(&P.d_cinv, checksum_vec(M, true, idx == p->passes - 1 ? 1.0 / (double)p->n : 1.0))) != TFFT_OK)
-        return rc;
-    std::vector<double> kappa = checksum_kappa(M, false);
-    const std::vector<double> inv = checksum_kappa(M, true);
-    kappa.insert(kappa.end(), inv.begin(), inv.end());
-    return upload(&P.d_kappa, kappa);
+    // the binary64 tables in one allocation
+    const std::vector<cd> fwd = checksum_roots(M, false), inv = checksum_roots(M, true);
+    std::vector<double> all = w64;
+    auto append = [&](const std::vector<double> &t) { all.insert(all.end(), t.begin(), t.end()); };
+    append(checksum_vec(fwd, 1.0));
+    append(checksum_vec(inv, 1.0));
+    append(checksum_vec(inv, idx == p->passes - 1 ? 1.0 / (double)p->n : 1.0));
+    const bool kappa = fp64 && p->tile;
+    if (kappa) {
+        append_kappa(&all, fwd);
+        append_kappa(&all, inv);
+    }
+    if ((rc = upload(&P.d_stw64, all)) != TFFT_OK) return rc;
+    P.d_cfwd = P.d_stw64 + 2 * (size_t)M;
+    P.d_cinv_unscaled = P.d_cfwd + 2 * (size_t)M;
+    P.d_cinv = P.d_cinv_unscaled + 2 * (size_t)M;
+    P.d_kappa = kappa ? P.d_cinv + 2 * (size_t)M : nullptr;
+    return TFFT_OK;
 }
 
 void free_plan(tfft_plan_s *p) {
@@ -307,20 +317,14 @@ void free_plan(tfft_plan_s *p) {
     for (auto &P : p->pass) {
         (void)hipFree(P.d_stw);
         (void)hipFree(P.d_stw64);
-        (void)hipFree(P.d_cfwd);
-        (void)hipFree(P.d_cinv);
-        (void)hipFree(P.d_cinv_unscaled);
-        (void)hipFree(P.d_kappa);
         (void)hipFree(P.d_fault_head);
         (void)hipFree(P.d_faults);
     }
     (void)hipFree(p->d_itw_lo);
     (void)hipFree(p->d_itw_hi);
     (void)hipFree(p->d_work);
-    (void)hipFree(p->d_rep);
-    (void)hipFree(p->d_recs);
+    (void)hipFree(p->d_rep);  // with the records, tickets and partial sums
     (void)hipFree(p->d_sig_off);
-    (void)hipFree(p->d_tile);
     for (auto &e : p->ev)
         if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(cur);
@@ -460,7 +464,7 @@ PassArgs pass_args(const tfft_plan_s *p, int i, const ChunkGeom &cg, int64_t nb,
     A.conj_out = inverse ? 1 : 0;
     A.out_scale = (inverse && last && !(p->flags & TFFT_INVERSE_UNSCALED)) ? 1.0 / (double)p->n : 1.0;
     A.cvec = !inverse ? P.d_cfwd : ((p->flags & TFFT_INVERSE_UNSCALED) ? P.d_cinv_unscaled : P.d_cinv);
-    A.ckappa = P.d_kappa + (inverse ? P.M : 0);
+    A.ckappa = P.d_kappa ? P.d_kappa + (inverse ? P.M : 0) : nullptr;
     const cd cf = checksum_factor(P.M) * A.out_scale;
     A.cf_re = cf.real();
     A.cf_im = cf.imag();
@@ -567,6 +571,8 @@ int pass_split_log2(const tfft_plan_s *p, const PassPlan &P) {
         return 0;
     int cus = 0;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
+    // (2048 threads are the most that a CU holds: no query where the groups fill that)
+    if (P.n_groups * cfg_threads(p->dtype == TFFT_C128, P.M, P.kind) >= (int64_t)cus * 2048) return 0;
     const int64_t resident = (int64_t)cus * std::max(1, pass_occupancy(p->dtype == TFFT_C128, P.M, P.kind, FT_BLOCK));
     int k = 0;
     while ((P.n_groups << k) < resident && (P.G / P.C) >> (k + 1) >= 1) ++k;
@@ -804,10 +810,12 @@ int shape_plan(tfft_plan_s *p, int64_t n, int64_t batch, int dtype, const tfft_o
     return TFFT_OK;
 }
 
-// The memory of groups that several workgroups share: the tickets (shared by the
-// passes, which run one after the other, and zero between launches) and the
-// partial sums (shared as well).
-int tile_buffers(tfft_plan_s *p) {
+// The plan's report memory, one allocation: the counters, the tickets of groups
+// that several workgroups share (shared by the passes, which run one after the
+// other, and zero between launches), the records, behind them what
+// read_tile_report gathers (tile launches), the shared groups' partial sums
+// (shared by the passes as well).
+int report_buffers(tfft_plan_s *p) {
     int64_t parts = 0, groups = 0, all = 0;
     for (int i = 0; i < p->passes; ++i) {
         PassPlan &P = p->pass[i];
@@ -820,19 +828,24 @@ int tile_buffers(tfft_plan_s *p) {
         }
         all += P.n_groups;
     }
-    if (groups == 0) return TFFT_OK;
-    const size_t tick_bytes = sizeof(uint32_t) * kTickStride * (size_t)groups;
-    if (hipMalloc(&p->d_tile, tick_bytes + sizeof(double) * 5 * (size_t)parts) != hipSuccess) {
-        p->d_tile = nullptr;
-        return TFFT_E_NOMEM;
-    }
-    const std::vector<char> zero(tick_bytes, 0);  // (a copy: as for the report)
-    if (hipMemcpy(p->d_tile, zero.data(), zero.size(), hipMemcpyHostToDevice) != hipSuccess) return TFFT_E_HIP;
+    const size_t rep = 256;
+    const size_t tick = sizeof(uint32_t) * kTickStride * (size_t)groups;
+    const size_t recs = sizeof(DevRecord) * (size_t)p->rec_cap;
+    const size_t gather = p->tile ? sizeof(DevReport) + sizeof(DevRecord) * (size_t)std::min(kGatherRecords, p->rec_cap) : 0;
+    const size_t part = sizeof(double) * 5 * (size_t)parts;
+    static_assert(sizeof(DevReport) <= 256 && sizeof(DevReport) % 16 == 0 && sizeof(DevRecord) % 16 == 0, "report layout");
+    char *base = nullptr;
+    if (hipMalloc((void **)&base, rep + tick + recs + gather + part) != hipSuccess) return TFFT_E_NOMEM;
+    p->d_rep = reinterpret_cast<DevReport *>(base);
+    p->d_recs = reinterpret_cast<DevRecord *>(base + rep + tick);
     for (int i = 0; i < p->passes; ++i) {
-        TileArgs &T = p->pass[i].tile;
-        T.tick = static_cast<uint32_t *>(p->d_tile);
-        T.part = reinterpret_cast<double *>(static_cast<char *>(p->d_tile) + tick_bytes);
+        p->pass[i].tile.tick = reinterpret_cast<uint32_t *>(base + rep);
+        p->pass[i].tile.part = reinterpret_cast<double *>(base + rep + tick + recs + gather);
     }
+    // tile launches: no group flagged before the first execution, which may be
+    // on a stream that does not wait for the null stream
+    if (hipMemset(base, 0, rep + tick + (p->tile ? recs : 0)) != hipSuccess) return TFFT_E_HIP;
+    if ((p->tile || tick > 0) && hipStreamSynchronize(nullptr) != hipSuccess) return TFFT_E_HIP;
     return TFFT_OK;
 }
 
@@ -852,6 +865,7 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
     }
     (void)hipGetDevice(&p->device);
     p->extent = host_off ? extent : n * batch;
+    choose_forms(p);
     for (int i = 0; i < p->passes && rc == TFFT_OK; ++i) rc = upload_pass(p, i);
     if (rc == TFFT_OK && p->passes > 1) {
         // w_N^t = lo[t mod 2^b] * hi[t >> b]
@@ -876,25 +890,7 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
             rc = TFFT_E_NOMEM;
         }
     }
-    choose_forms(p);
-    if (rc == TFFT_OK) {
-        const size_t rec_bytes = sizeof(DevRecord) * (size_t)p->rec_cap;
-        // tile launches: behind the records what read_tile_report gathers
-        const size_t gather_bytes =
-            p->tile ? sizeof(DevReport) + sizeof(DevRecord) * (size_t)std::min(kGatherRecords, p->rec_cap) : 0;
-        const DevReport zero{};
-        // tile launches: no group flagged before the first execution.  (The
-        // copy, unlike the memset, is complete when it returns, and with it the
-        // memset before it: the first execution may be on a stream that does
-        // not wait for the null stream)
-        if (hipMalloc((void **)&p->d_rep, sizeof(DevReport)) != hipSuccess ||
-            hipMalloc((void **)&p->d_recs, rec_bytes + gather_bytes) != hipSuccess)
-            rc = TFFT_E_NOMEM;
-        else if ((p->tile && hipMemset(p->d_recs, 0, rec_bytes) != hipSuccess) ||
-                 hipMemcpy(p->d_rep, &zero, sizeof(zero), hipMemcpyHostToDevice) != hipSuccess)
-            rc = TFFT_E_HIP;
-    }
-    if (rc == TFFT_OK) rc = tile_buffers(p);
+    if (rc == TFFT_OK) rc = report_buffers(p);
     if (rc == TFFT_OK && host_off) {
         std::vector<int64_t> off(host_off, host_off + batch);
         rc = upload(&p->d_sig_off, off);
@@ -2034,7 +2030,7 @@ int tfft_host_root(int64_t t, int64_t n, double *out) {
 
 int tfft_host_checksum_vector(int64_t m, int inverse, double scale, double *out) {
     if (!out || m < 2 || m > (int64_t(1) << 24) || (m & (m - 1)) != 0 || !std::isfinite(scale)) return TFFT_E_INVALID;
-    const std::vector<double> c = checksum_vec((int)m, inverse != 0, scale);
+    const std::vector<double> c = checksum_vec(checksum_roots((int)m, inverse != 0), scale);
     std::memcpy(out, c.data(), sizeof(double) * c.size());
     return TFFT_OK;
 }
