@@ -480,16 +480,13 @@ static hipError_t launch_cols_one(const PassArgs &a, int grid, hipStream_t st) {
 
 template <typename R, int M>
 hipError_t cols_m(int kind, int ft, const PassArgs &a, int grid, hipStream_t st) {
-    if constexpr (cfg_cols(sizeof(R) == 8, M, KIND_STRIDED)) {
-        if (kind == KIND_STRIDED)
-            return ft ? launch_cols_one<R, M, KIND_STRIDED, FT_BLOCK>(a, grid, st)
-                      : launch_cols_one<R, M, KIND_STRIDED, FT_NONE>(a, grid, st);
-    }
-    if constexpr (cfg_cols(sizeof(R) == 8, M, KIND_LAST)) {
-        if (kind == KIND_LAST)
-            return ft ? launch_cols_one<R, M, KIND_LAST, FT_BLOCK>(a, grid, st)
-                      : launch_cols_one<R, M, KIND_LAST, FT_NONE>(a, grid, st);
-    }
+    static_assert(cfg_cols(sizeof(R) == 8, M, KIND_STRIDED) && cfg_cols(sizeof(R) == 8, M, KIND_LAST), "column kernel shape");
+    if (kind == KIND_STRIDED)
+        return ft ? launch_cols_one<R, M, KIND_STRIDED, FT_BLOCK>(a, grid, st)
+                  : launch_cols_one<R, M, KIND_STRIDED, FT_NONE>(a, grid, st);
+    if (kind == KIND_LAST)
+        return ft ? launch_cols_one<R, M, KIND_LAST, FT_BLOCK>(a, grid, st)
+                  : launch_cols_one<R, M, KIND_LAST, FT_NONE>(a, grid, st);
     return hipErrorInvalidValue;
 }
 

@@ -493,7 +493,7 @@ void *scratch_address(int device);
 // Host-side launchers (defined in the kernel translation unit).
 hipError_t launch_pass(int fp64, int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st);
 hipError_t launch_correct(int fp64, int M, int kind, const PassArgs &a, int grid, hipStream_t st);
-hipError_t launch_cols(int fp64, int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st);
+hipError_t launch_cols(int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st);
 hipError_t launch_tile(int fp64, int M, int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st);
 hipError_t launch_reset(DevReport *rep, hipStream_t st);
 hipError_t launch_gather(const DevRecord *recs, int64_t n, DevReport *rep, DevRecord *out, int64_t cap, hipStream_t st);

@@ -10,8 +10,10 @@ namespace tfft {
 
 TFFT_FOR_EACH_M(TFFT_EXTERN_M, float)
 TFFT_FOR_EACH_M(TFFT_EXTERN_M, double)
-TFFT_FOR_EACH_M(TFFT_EXTERN_COLS, float)
-TFFT_FOR_EACH_M(TFFT_EXTERN_COLS, double)
+TFFT_EXTERN_COLS(float, 64)
+TFFT_EXTERN_COLS(float, 128)
+TFFT_EXTERN_COLS(float, 256)
+TFFT_EXTERN_COLS(float, 512)
 TFFT_PERSIST_EXTERN(float, FT_NONE)
 TFFT_PERSIST_EXTERN(float, FT_BLOCK)
 TFFT_PERSIST_EXTERN(double, FT_NONE)
@@ -57,9 +59,14 @@ hipError_t launch_correct(int fp64, int M, int kind, const PassArgs &a, int grid
     return by_m<float>(M, [&](auto m) { return correct_m<float, decltype(m)::value>(kind, a, grid, st); });
 }
 
-hipError_t launch_cols(int fp64, int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st) {
-    if (fp64) return by_m<double>(M, [&](auto m) { return cols_m<double, decltype(m)::value>(kind, ft, a, grid, st); });
-    return by_m<float>(M, [&](auto m) { return cols_m<float, decltype(m)::value>(kind, ft, a, grid, st); });
+hipError_t launch_cols(int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st) {
+    switch (M) {
+        case 64: return cols_m<float, 64>(kind, ft, a, grid, st);
+        case 128: return cols_m<float, 128>(kind, ft, a, grid, st);
+        case 256: return cols_m<float, 256>(kind, ft, a, grid, st);
+        case 512: return cols_m<float, 512>(kind, ft, a, grid, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_tile(int fp64, int M, int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st) {

@@ -663,7 +663,7 @@ int exec(tfft_plan_s *p, const void *d_in, void *d_out, int mode, void *stream, 
                 const int64_t most = p->grid_scale >= 0 ? (int64_t)TFFT_COL_GRID << p->grid_scale
                                                         : (int64_t)TFFT_COL_GRID >> -p->grid_scale;
                 const int grid = (int)std::min<int64_t>((cg.n_groups + 7) / 8 * 8, most * (P.M == 64 ? 2 : 1));
-                e = launch_cols(fp64, P.M, P.kind, kft, A, grid, st);
+                e = launch_cols(P.M, P.kind, kft, A, grid, st);
             } else {
                 e = launch_pass(fp64, P.M, P.kind, kft, A, cg.grid, st);
             }
