@@ -1802,8 +1802,10 @@ hipError_t tile_m(int kind, int ft, const PassArgs &a, const TileArgs &t, hipStr
     if constexpr (M <= 4096) {
         if (kind == KIND_ROWS) return launch_tile_one<R, M, KIND_ROWS>(ft, a, t, st);
     }
-    if constexpr (M >= 16 && M <= 1024) {
+    if constexpr (M >= 16 && M <= 512) {
         if (kind == KIND_STRIDED) return launch_tile_one<R, M, KIND_STRIDED>(ft, a, t, st);
+    }
+    if constexpr (M >= 16 && M <= 1024) {
         if (kind == KIND_LAST) return launch_tile_one<R, M, KIND_LAST>(ft, a, t, st);
     }
     return hipErrorInvalidValue;

@@ -512,35 +512,45 @@ int tile_split_log2(const tfft_plan_s *p, const PassPlan &P) {
 // Whether a plan runs as tile launches.  A pass kernel has one workgroup per
 // checksum group, so a batch of few groups leaves most of the chip idle; its
 // tiles, spread over the chip, take over where every pass's launch would hold
-// few wavefronts.  Measured (us per call, pass kernels then tiles; FT CORRECT /
-// OFF): complex64 N = 256 at 2^14 elements (4 wavefronts) 18 -> 6 / 15 -> 3.5;
-// N = 1024 at 2^20 (64) 78 -> 11 / 70 -> 8; N = 2^14 at 2^20 (1024) 27 -> 19 /
-// 19 -> 13; N = 2^16 at 2^21 (1024) 40 -> 33 / 30 -> 20, at 2^22 (2048) 44 -> 56
-// / 35 -> 33: the line lies at 1024 wavefronts.  It lies lower for rows of 1024
-// points and more, whose pass kernel shares a group between workgroups as well
-// (pass_split_log2) but holds the tables in registers: complex64 N = 1024 at
-// 2^23 (512) 39 -> 44 / 34 -> 34, at 2^22 (256) 25 -> 26 / 20 -> 18; N = 4096 at
-// 2^22 (512) 26 -> 31 / 21 -> 24, at 2^21 (256) 20 -> 16 / 15 -> 14; complex128
-// N = 1024 at 2^24 (1024) 115 -> 133 / 116 -> 123, at 9968 signals (624) 94 ->
-// 85, at 2^23 (512) 67 -> 69 / 64 -> 60, N = 4096 at 2^23 (1024) 77 -> 87 / 87 -> 67; and for strided passes of 1024
-// (complex128 N = 2^20 at 128 wavefronts 44 -> 36 / 38 -> 32, at 512 83 -> 106 /
-// 80 -> 73).  Signals of up to 16 points always run as tiles: their pass kernels
-// hold less than a wavefront per workgroup (complex64 N = 16 at 2^24 154 -> 85 /
-// 146 -> 79), up to the 2^32 - 1 threads of a launch (one workgroup per group,
-// where the pass kernels walk over the groups).  A plan with a grid_scale or a
-// chunk of its own keeps the pass kernels those describe.
+// few wavefronts (groups times wavefronts of the pass kernel's workgroup): up to
+// 1024, one per SIMD.  Measured at the line, us per call, the form that would run
+// otherwise then tiles, FT CORRECT and OFF:
+//   complex64  N = 64    13.7 -> 12.2,  9.7 ->  7.1   N = 512   37.1 -> 37.6, 31.7 -> 26.7
+//              N = 2^14  22.5 -> 19.3, 17.1 -> 12.7   N = 2^18  54.4 -> 39.4, 44.9 -> 26.1
+//   complex128 N = 256   30.6 -> 25.9, 26.0 -> 22.9   N = 512   50.9 -> 53.5, 48.7 -> 44.6
+//              N = 2^14  33.8 -> 23.2, 27.0 -> 18.4   N = 2^18   101 -> 77.3, 97.7 -> 54.1
+// Rows of 1024 points and more have a pass kernel that shares a group between
+// workgroups too (pass_split_log2) and keeps its tables in registers, and there
+// the two modes part: the checksum's tables, read again for every tile, cost
+// more than the better spread gives well before it stops paying without them.  One
+// line serves both modes, between the two: 256 wavefronts for complex64,
+//   N = 1024 (256) 24.0 -> 25.7, 19.2 -> 18.1   (512) 37.8 -> 43.3, 33.4 -> 33.6
+//   N = 4096 (256) 19.4 -> 19.6, 14.2 -> 12.3   (512) 24.4 -> 38.2, 20.0 -> 23.8
+// (N = 2048 loses on either side of it: 24.2 -> 27.6, 19.3 -> 22.0), 768 for
+// complex128 and 1024 for its N = 4096, whose pass kernel is the slower one
+// without the checksum,
+//   N = 1024 (512) 56.4 -> 55.3, 57.1 -> 46.5   (768) 85.9 -> 98.2, 86.7 -> 91.4
+//   N = 2048 (512) 59.4 -> 60.0, 65.7 -> 49.4   (768) 90.8 ->  101,  100 ->  100
+//   N = 4096 (512) 41.5 -> 46.6, 46.1 -> 34.5   (1024) 68.8 -> 79.5, 81.2 -> 60.0.
+// Strided passes of 1024 points have 1024 wavefronts and more whatever the batch
+// and keep the pass kernel (complex128 N = 2^20, one signal 42.4 -> 38.4, 37.3 ->
+// 33.8, two 51.2 -> 56.8, 46.4 -> 36.8, four 79.9 -> 99.5, 76.1 -> 65.8).  Signals
+// of up to 16 points always run as tiles: their pass kernels hold less than a
+// wavefront per workgroup (complex64 N = 16 at 2^24 154 -> 85 / 146 -> 79), up to
+// the 2^32 - 1 threads of a launch (one workgroup per group, where the pass
+// kernels walk over the groups).  A plan with a grid_scale or a chunk of its own
+// keeps the pass kernels those describe.
 bool use_tiles(const tfft_plan_s *p) {
     if (p->persistent || p->scheme != TFFT_SCHEME_BLOCK || p->grid_scale != 0 || p->chunk < p->batch) return false;
     const int fp64 = p->dtype == TFFT_C128;
     bool few = true, small = true;
     for (int i = 0; i < p->passes; ++i) {
         const PassPlan &P = p->pass[i];
-        if (tile_rounds(p, P) < 1) return false;
+        if (tile_rounds(p, P) < 1 || (P.kind == KIND_STRIDED && P.M >= 1024)) return false;
         if ((P.n_groups + 7) / 8 * 8 * cfg_tile_threads(fp64, P.M, P.kind) > UINT32_MAX) return false;
         const int threads = cfg_threads(fp64, P.M, P.kind);
         int64_t limit = TFFT_TILE_MAX_WAVES;
         if (P.kind == KIND_ROWS && P.M >= 1024) limit = limit * (fp64 ? (P.M >= 4096 ? 4 : 3) : 1) / 4;
-        if (P.kind == KIND_STRIDED && P.M >= 1024) limit /= 4;
         small = small && threads < 64;
         few = few && P.n_groups * ((threads + 63) / 64) <= limit;
     }
