@@ -141,7 +141,10 @@ typedef struct {
     int32_t pass_len[TFFT_MAX_PASSES];     /* transform length of each pass, product = n */
     int32_t group[TFFT_MAX_PASSES];        /* checksum group size of each pass           */
     int32_t elems_per_thread[TFFT_MAX_PASSES];
-    int32_t tile_signals[TFFT_MAX_PASSES]; /* sub-signals held in LDS by one workgroup   */
+    int32_t tile_signals[TFFT_MAX_PASSES]; /* strip width C of the checksum group layout
+                                              (tfft_record); a workgroup may hold more
+                                              or fewer of a group's members at a time,
+                                              by the pass's launch form             */
     int32_t stages[TFFT_MAX_PASSES];
     int32_t radices[TFFT_MAX_PASSES][8];   /* butterfly radix of each stage of each pass */
     int64_t groups[TFFT_MAX_PASSES];       /* checksum groups per pass                   */
@@ -163,7 +166,7 @@ typedef struct {
 /* One flagged group.
  * Checksum groups: in a one-pass plan, group g of G = group[0] members holds
  * signals g*G .. g*G+G-1 (member b = signal g*G + b; the last group may be
- * partial).  In pass p of a multi-pass plan (tile C = tile_signals[p],
+ * partial).  In pass p of a multi-pass plan (strip width C = tile_signals[p],
  * G = group[p], rb = G / C), the sub-transforms are numbered per signal as
  * in tfft_fault (sub = o * S_p + i in a strided pass, sub = output row r in
  * the last pass); an "outer unit" is one block o of one signal (strided
@@ -255,11 +258,12 @@ int tfft_exec_inverse(tfft_plan p, const void *d_in, void *d_out, int ft_mode, v
  * tfft_exec_forward (inverse == 0) or tfft_exec_inverse (inverse != 0) on the
  * same plan and buffers, but the execution's report counters, records and
  * multi-pass workspace live in the library's static device scratch of
- * TFFT_SCRATCH_BYTES instead of the plan's buffers; the call allocates
+ * TFFT_SCRATCH_BYTES instead of the plan's buffers (the tickets and partial
+ * sums of groups that several workgroups share stay the plan's); the call allocates
  * nothing (no hipMalloc, no hipFree, no allocating library routine).  The
  * caller passes the input and output buffers as for tfft_exec_forward.
  * Returns E_SCRATCH when the report and workspace of the plan need more than
- * TFFT_SCRATCH_BYTES (about 64 B per checksum group plus, for multi-pass
+ * TFFT_SCRATCH_BYTES (about 80 B per checksum group plus, for multi-pass
  * plans, n * batch elements, or n * chunk with tfft_options.chunk), else as
  * tfft_exec_forward.  Every call on one device shares that device's scratch
  * and leaves the last call's contents there: tfft_get_report on this plan

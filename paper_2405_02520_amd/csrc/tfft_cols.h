@@ -22,7 +22,9 @@ namespace tfft {
 // Bound by HBM (16 bytes per element and pass) and, with the checksum, close to
 // it by instruction issue.  128 registers, so that 16 wavefronts per CU hide
 // each other's exchanges with the next tile's loads in flight, where the pass
-// kernels hold 190-240 and 8.  Measured at 1 GiB, FT CORRECT, us of the first and
+// kernels hold 190-240 and 8.  (The checksummed strided kernel of 256 points needs
+// 8 more: 16 bytes a lane go to scratch and back once per group, outside the tile
+// loop; with offset tables 2 registers do in every tile.)  Measured at 1 GiB, FT CORRECT, us of the first and
 // the last pass, pass kernels then columns: N = 2^13 531 + 535 -> 432 + 464 (4.0
 // -> 4.8 TB/s), 2^17 605 + 540 -> 541 + 490; N = 2^19 first pass (M = 512) 670 ->
 // 545; N = 2^19 with the checksum off 629 -> 509 in all.
@@ -73,7 +75,8 @@ __global__ void __launch_bounds__(cfg_col_threads(M)) col_kernel(PassArgs args) 
     constexpr bool BLK = Cf::BLK;
     constexpr int E = Cf::E, T = Cf::T, WV = Cf::WV, C = Cf::C, NSTAGE = Cf::NSTAGE, MB = Cf::MB, PW = Cf::PW;
     // the next tile's loads ahead; not where the fault hook leaves no registers for
-    // them (the strided passes of 256 and 512 points would spill in every tile)
+    // them (the strided passes of 256 and 512 points would spill in every tile; as
+    // they are, they and the hooked last passes spill 8 registers once per group)
     constexpr bool AHEAD = !(HOOK && KIND == KIND_STRIDED && M >= 256);
     using St = Stages<M, E>;
     __shared__ __align__(16) cx<R> lds[Cf::NBUF][M * MB];
