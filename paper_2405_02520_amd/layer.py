@@ -18,42 +18,55 @@ import torch
 
 from . import Plan
 
-# shape -> {stream handle: (forward plan, adjoint plan)}.  A plan must not run on
-# two streams at once (it owns its workspace, tickets and report), so every
-# stream has its own.
-_PLANS: dict = {}
-_LAST: dict = {}  # shape -> {"forward" | "backward": the plan that last executed}
-_LOCK = threading.Lock()  # the backward passes run on autograd's threads
+class _Shape:
+    """The plans of one (length, batch, dtype, device).  A plan must not run on
+    two streams at once (it owns its workspace, tickets and report), so every
+    stream has a pair of its own."""
 
+    def __init__(self, n, batch, dtype, device):
+        self.args = (n, batch, dtype)
+        self.device = device
+        self.name = (n, batch, str(dtype), str(device))
+        self.pairs: dict = {}  # stream handle -> (forward plan, adjoint plan)
+        self.last = [None, None]  # the plans that last executed, forward and adjoint
 
-def _key(n: int, batch: int, dtype, device) -> tuple:
-    return (n, batch, str(dtype), str(device))
+    def pair(self, stream) -> tuple[Plan, Plan]:
+        return self.pairs.get(stream.cuda_stream) or self._new_pair(stream.cuda_stream)
 
-
-def _plans(n: int, batch: int, dtype, device, stream=None) -> tuple[Plan, Plan]:
-    st = (stream if stream is not None else torch.cuda.current_stream(device)).cuda_stream
-    with _LOCK:
-        pairs = _PLANS.setdefault(_key(n, batch, dtype, device), {})
-        if st not in pairs:
-            with torch.cuda.device(device):
-                if pairs and torch.cuda.is_current_stream_capturing():
+    def _new_pair(self, st) -> tuple[Plan, Plan]:
+        with _LOCK, torch.cuda.device(self.device):
+            if st not in self.pairs:
+                if self.pairs and torch.cuda.is_current_stream_capturing():
                     # nothing can be allocated while a graph is captured: the
                     # graph takes over the pair of the warm-up, and that stream
                     # gets a new one when it next needs it
-                    pairs[st] = pairs.pop(next(reversed(pairs)))
+                    self.pairs[st] = self.pairs.pop(next(reversed(self.pairs)))
                 else:
-                    pairs[st] = (Plan(n, batch, dtype), Plan(n, batch, dtype, inverse_unscaled=True))
-        return pairs[st]
+                    self.pairs[st] = (Plan(*self.args), Plan(*self.args, inverse_unscaled=True))
+            return self.pairs[st]
+
+
+_SHAPES: dict = {}
+_LOCK = threading.Lock()  # the backward passes run on autograd's threads
+
+
+def _shape(n: int, batch: int, dtype, device) -> _Shape:
+    key = (n, batch, dtype, device)
+    return _SHAPES.get(key) or _SHAPES.setdefault(key, _Shape(*key))
+
+
+def _plans(n: int, batch: int, dtype, device) -> tuple[Plan, Plan]:
+    return _shape(n, batch, dtype, device).pair(torch.cuda.current_stream(device))
 
 
 def clear_plan_cache() -> None:
     with _LOCK:
-        for pairs in _PLANS.values():
-            for fwd, adj in pairs.values():
+        for shape in _SHAPES.values():
+            for fwd, adj in shape.pairs.values():
                 fwd.close()
                 adj.close()
-        _PLANS.clear()
-        _LAST.clear()
+            shape.pairs.clear()
+        _SHAPES.clear()
 
 
 class UncorrectableError(RuntimeError):
@@ -72,24 +85,21 @@ class _FFTFunction(torch.autograd.Function):
         n = x.shape[-1]
         batch = x.numel() // n
         st = torch.cuda.current_stream(x.device)
-        fwd, _ = _plans(n, batch, x.dtype, x.device, st)
+        ctx.shape = shape = _shape(n, batch, x.dtype, x.device)
+        fwd = shape.last[0] = shape.pair(st)[0]
         ctx.ft_mode = ft_mode
         ctx.check = check
         xc = x.contiguous()
         y = fwd.forward(xc, ft_mode=ft_mode, stream=st).view(x.shape)
-        _LAST.setdefault(_key(n, batch, x.dtype, x.device), {})["forward"] = fwd
         if check and ft_mode == "correct":
             _verify(fwd, "forward transform")
         return y
 
     @staticmethod
     def backward(ctx, gy):
-        n = gy.shape[-1]
         st = torch.cuda.current_stream(gy.device)
-        batch = gy.numel() // n
-        _, adj = _plans(n, batch, gy.dtype, gy.device, st)
+        adj = ctx.shape.last[1] = ctx.shape.pair(st)[1]
         gx = adj.inverse(gy.contiguous(), ft_mode=ctx.ft_mode, stream=st)
-        _LAST.setdefault(_key(n, batch, gy.dtype, gy.device), {})["backward"] = adj
         if ctx.check and ctx.ft_mode == "correct":
             _verify(adj, "backward transform")
         return gx.view(gy.shape), None, None
@@ -115,7 +125,7 @@ def last_reports():
     (length, batch, dtype, device)."""
     with _LOCK:
         last = {}
-        for key, pairs in _PLANS.items():
-            for fwd, adj in pairs.values():
-                last[key] = {"forward": fwd, "backward": adj, **_LAST.get(key, {})}
-    return {key: {way: plan.report() for way, plan in ways.items()} for key, ways in last.items()}
+        for shape in _SHAPES.values():
+            for pair in shape.pairs.values():
+                last[shape.name] = [ran or plan for ran, plan in zip(shape.last, pair)]
+    return {name: {"forward": fwd.report(), "backward": adj.report()} for name, (fwd, adj) in last.items()}
