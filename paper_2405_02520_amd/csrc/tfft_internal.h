@@ -496,7 +496,8 @@ hipError_t launch_correct(int fp64, int M, int kind, const PassArgs &a, int grid
 hipError_t launch_cols(int M, int kind, int ft, const PassArgs &a, int grid, hipStream_t st);
 hipError_t launch_tile(int fp64, int M, int kind, int ft, const PassArgs &a, const TileArgs &t, hipStream_t st);
 hipError_t launch_reset(DevReport *rep, hipStream_t st);
-hipError_t launch_gather(const DevRecord *recs, int64_t n, DevReport *rep, DevRecord *out, int64_t cap, hipStream_t st);
+hipError_t launch_gather(const DevRecord *recs, int64_t n, DevReport *rep, DevRecord *out, int64_t cap,
+                         unsigned long long base, hipStream_t st);
 // Persistent ragged kernel: launch over `grid` workgroups, its resident
 // workgroups per compute unit, and the reset of its queue state and report.
 hipError_t launch_persist(int fp64, int ft, const PQueue &q, int grid, hipStream_t st);

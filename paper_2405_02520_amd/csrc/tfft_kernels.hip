@@ -152,22 +152,23 @@ hipError_t launch_persist_reset(const PQueue &q, int n_done, DevReport *rep, hip
     return hipGetLastError();
 }
 
-// The flagged ones (action not 0) of n records, counted and the first `cap` of
-// them gathered; `rep` is zero before.
+// The flagged ones (action not 0) of n records, added to the counters and the
+// first `cap` of them gathered; the counters run on, `base` flagged so far.
 __global__ void __launch_bounds__(256) gather_kernel(const DevRecord *recs, int64_t n, DevReport *rep, DevRecord *out,
-                                                     int64_t cap) {
+                                                     int64_t cap, unsigned long long base) {
     for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         const int32_t action = recs[i].action;
         if (action == 0) continue;
-        const unsigned long long k = atomicAdd(&rep->n_flag, 1ULL);
+        const unsigned long long k = atomicAdd(&rep->n_flag, 1ULL) - base;
         if ((int64_t)k < cap) out[k] = recs[i];
         if (action > 1) atomicAdd(action == 2 ? &rep->corrected : action == 3 ? &rep->benign : &rep->uncorrectable, 1ULL);
     }
 }
 
-hipError_t launch_gather(const DevRecord *recs, int64_t n, DevReport *rep, DevRecord *out, int64_t cap, hipStream_t st) {
+hipError_t launch_gather(const DevRecord *recs, int64_t n, DevReport *rep, DevRecord *out, int64_t cap,
+                         unsigned long long base, hipStream_t st) {
     const unsigned grid = (unsigned)std::min<int64_t>(1024, (n + 255) / 256);
-    hipLaunchKernelGGL(gather_kernel, dim3(grid), dim3(256), 0, st, recs, n, rep, out, cap);
+    hipLaunchKernelGGL(gather_kernel, dim3(grid), dim3(256), 0, st, recs, n, rep, out, cap, base);
     return hipGetLastError();
 }
 

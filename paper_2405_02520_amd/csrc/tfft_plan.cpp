@@ -117,12 +117,14 @@ struct tfft_plan_s {
     int persistent = 0;          // shaped for the persistent ragged kernel (tiles of 512 threads)
     int grid_scale = 0;
     int tile = 0;                // runs as tile launches (use_tiles)
-    std::mutex gather_mu;        // tile launches: reports gathered behind the records, one at a time
+    std::mutex gather_mu;        // tile launches: reports gathered behind the records, one at a time;
+    DevReport gathered{};        // the running counters there, as last read
 };
 
 namespace {
 
 constexpr int64_t kGatherRecords = 4096;  // 320 KiB
+constexpr int64_t kDirectRecords = 128;   // 10 KiB: copied as quickly as the counters
 
 int ilog2_64(int64_t x) {
     int k = 0;
@@ -841,7 +843,8 @@ int report_buffers(tfft_plan_s *p) {
     const size_t rep = 256;
     const size_t tick = sizeof(uint32_t) * kTickStride * (size_t)groups;
     const size_t recs = sizeof(DevRecord) * (size_t)p->rec_cap;
-    const size_t gather = p->tile ? sizeof(DevReport) + sizeof(DevRecord) * (size_t)std::min(kGatherRecords, p->rec_cap) : 0;
+    const bool gathers = p->tile && p->rec_cap > kDirectRecords;
+    const size_t gather = gathers ? sizeof(DevReport) + sizeof(DevRecord) * (size_t)std::min(kGatherRecords, p->rec_cap) : 0;
     const size_t part = sizeof(double) * 5 * (size_t)parts;
     static_assert(sizeof(DevReport) <= 256 && sizeof(DevReport) % 16 == 0 && sizeof(DevRecord) % 16 == 0, "report layout");
     char *base = nullptr;
@@ -853,8 +856,9 @@ int report_buffers(tfft_plan_s *p) {
         p->pass[i].tile.part = reinterpret_cast<double *>(base + rep + tick + recs + gather);
     }
     // tile launches: no group flagged before the first execution, which may be
-    // on a stream that does not wait for the null stream
-    if (hipMemset(base, 0, rep + tick + (p->tile ? recs : 0)) != hipSuccess) return TFFT_E_HIP;
+    // on a stream that does not wait for the null stream, and none gathered
+    const size_t zero = rep + tick + (p->tile ? recs : 0) + (gathers ? sizeof(DevReport) : 0);
+    if (hipMemset(base, 0, zero) != hipSuccess) return TFFT_E_HIP;
     if ((p->tile || tick > 0) && hipStreamSynchronize(nullptr) != hipSuccess) return TFFT_E_HIP;
     return TFFT_OK;
 }
@@ -913,21 +917,39 @@ int create_plan(tfft_plan *out, int64_t n, int64_t batch, int dtype, const tfft_
     return TFFT_OK;
 }
 
-// The report of an execution as tile launches: the flagged groups' records and
-// the counters they add up to, gathered on the device (on the null stream, after
-// the caller's wait for the execution's), so that what is copied is the flagged
-// ones: all of them at once up to kGatherRecords, beyond by windows of as many
-// records.
+// The report of an execution as tile launches: the flagged groups' records
+// (action not 0) and the counters they add up to.  A few records are copied as
+// they are; of more, the flagged ones are gathered on the device (on the null
+// stream, after the caller's wait for the execution's) and copied, all of them
+// at once up to kGatherRecords, beyond by windows of as many records.
 int read_tile_report(tfft_plan_s *p, DevReport *h, std::vector<DevRecord> *recs) {
+    if (p->rec_cap <= kDirectRecords) {
+        recs->resize((size_t)p->rec_cap);
+        if (hipMemcpy(recs->data(), p->recs_last, sizeof(DevRecord) * recs->size(), hipMemcpyDeviceToHost) != hipSuccess)
+            return TFFT_E_HIP;
+        recs->erase(std::remove_if(recs->begin(), recs->end(), [](const DevRecord &r) { return r.action == 0; }),
+                    recs->end());
+        *h = DevReport{};
+        h->n_flag = recs->size();
+        for (const DevRecord &r : *recs) {
+            h->corrected += r.action == TFFT_ACT_CORRECTED;
+            h->benign += r.action == TFFT_ACT_BENIGN;
+            h->uncorrectable += r.action == TFFT_ACT_UNCORRECTABLE;
+        }
+        return TFFT_OK;
+    }
     std::lock_guard<std::mutex> lock(p->gather_mu);
     DevReport *cnt = reinterpret_cast<DevReport *>(p->d_recs + p->rec_cap);
     DevRecord *out = reinterpret_cast<DevRecord *>(cnt + 1);
     const int64_t cap = std::min(kGatherRecords, p->rec_cap);
     auto gather = [&](int64_t at, int64_t n, DevReport *c) -> bool {
-        if (launch_reset(cnt, nullptr) != hipSuccess ||
-            launch_gather(p->recs_last + at, n, cnt, out, cap, nullptr) != hipSuccess ||
-            hipMemcpy(c, cnt, sizeof(*c), hipMemcpyDeviceToHost) != hipSuccess)
+        const DevReport was = p->gathered;
+        DevReport &now = p->gathered;
+        if (launch_gather(p->recs_last + at, n, cnt, out, cap, was.n_flag, nullptr) != hipSuccess ||
+            hipMemcpy(&now, cnt, sizeof(now), hipMemcpyDeviceToHost) != hipSuccess)
             return false;
+        *c = {now.n_flag - was.n_flag, now.corrected - was.corrected, now.benign - was.benign,
+              now.uncorrectable - was.uncorrectable};
         if (c->n_flag == 0 || (int64_t)c->n_flag > cap) return true;
         const size_t k = recs->size();
         recs->resize(k + (size_t)c->n_flag);
