@@ -38,6 +38,7 @@ def layer(monkeypatch):
     monkeypatch.setattr(L, "Plan", FakePlan)
     monkeypatch.setattr(torch.cuda, "device", lambda d: contextlib.nullcontext())
     monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: types.SimpleNamespace(cuda_stream=L.at))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda i: L.at, raising=False)
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: FakePlan.capturing)
     monkeypatch.setattr(L, "at", 0, raising=False)
     yield L
@@ -63,6 +64,16 @@ def test_every_stream_has_its_own_plans(layer):
     assert {id(p) for p in pairs[0]}.isdisjoint({id(p) for p in pairs[1]})
     for st, pair in ((11, pairs[0]), (22, pairs[1])):
         assert all(set(p.ran) == {st} for p in pair)
+
+
+def test_backward_runs_with_the_plans_of_the_stream_it_is_called_on(layer):
+    layer.at = 11
+    _step(layer)
+    x = torch.randn(3, 8, dtype=torch.complex64, requires_grad=True)
+    y = layer.fft(x)
+    layer.at = 22
+    y.grad_fn.apply(torch.ones_like(y))  # outside autograd's engine
+    assert layer._plans(8, 3, torch.complex64, torch.device("cpu"))[1].ran == [22]
 
 
 def test_a_captured_graph_takes_over_the_warm_up_plans(layer):
